@@ -191,7 +191,7 @@ KERNEL_FAMILY = {"assemble_s1_fuel": ("k_assemble<float,p=2,fuel=true>",),
                  "sweep_x_A": ("k_wsweep<float,p=2,x-lines>", "k_csweep<2,32>", "k_csweep<2,16>"),
                  "sweep_y_M": ("k_wsweep<float,p=2,y-lines>",),
                  "sweep_y_cn": ("k_wsweep<float,p=2,y-lines>",)}
-SOURCES = {"k_assemble": ("assemble.hip",),
+SOURCES = {"k_assemble": ("assemble.h", "assemble.hip"),
            "k_wsweep": ("sweep_win.h", "sweep_kernels.h", "sweep.hip"),
            "k_csweep": ("sweep_col.h", "sweep_col.hip")}
 

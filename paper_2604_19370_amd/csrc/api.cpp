@@ -71,9 +71,12 @@ iga_status check_field(const void *p, const char *name)
 }
 
 // One step in place; the right-hand sides live in the plan's scratch buffers.
-// FP32 plans advance in increment form: the assembled right-hand sides are
+// Steps advance in increment form: the assembled right-hand sides are
 // R - (implicit operator) S, the solves give the increment, and the y sweep
-// adds the state it was taken from.  A PR or Strang step is six launches:
+// adds the state it was taken from.  FP32 needs it (the float right-hand side
+// then carries only the O(tau) change); FP64 gains the terms that are zero away
+// from the fire, the fuel sweeps and ambient elements among them, for one more
+// field read per y sweep.  A PR or Strang step is six launches:
 // assembly, x sweep, y sweep, twice; an explicit step is the first three.
 // The x sweeps solve in place, or into second scratch fields under a
 // column-wave x schedule (whose waves read rows around their own chunk).
@@ -85,13 +88,12 @@ void step_phases(const iga_plan *pl, void *T, void *fuel, StepPhases &sp, void *
     const bool col = pl->sched[0].col != 0;
     void *XR = col ? (work ? work[2] : pl->scratch_r2.ptr) : R;
     void *XRF = col ? (work ? work[3] : pl->scratch_rf2.ptr) : RF;
-    const void *bT = pl->delta ? T : nullptr, *bF = pl->delta ? fuel : nullptr;
-    const int add = pl->delta ? 1 : 0;
+    const void *bT = T, *bF = fuel;
     const bool pr = pl->d.scheme == IGA_PR;
     // substep 1 (PR: x implicit; Strang: S1) + the fuel right-hand side
-    // FP32 plans: the fuel increment vanishes exactly outside the burning
-    // region, and so do the windowed solves of it; those line blocks are skipped
-    const int zs = pl->delta ? 1 : 0;
+    // the fuel increment vanishes exactly outside the burning region, and so
+    // do the windowed solves of it; those line blocks are skipped
+    const int zs = 1;
     sp.a1 = AsmArgs{0, T, fuel, R, RF};
     sp.x1 = {{R, XR, OP_AX, -1, -1, nullptr, 0}, {RF, XRF, OP_MX, -1, -1, nullptr, 0, zs}};
     sp.two = true;
@@ -110,8 +112,8 @@ void step_phases(const iga_plan *pl, void *T, void *fuel, StepPhases &sp, void *
         sp.y2 = {{XR, T, OP_AY, -1, -1, bT, 0}, {XRF, fuel, OP_MY, -1, -1, bF, 0, zs}};
     } else {
         // S1's y solve fused with S2: T** = (A^y)^{-1} B^y T* along y, with
-        // T* = (M^y)^{-1} R (+ T^n in increment form)
-        sp.y1 = {{XR, T, OP_MY, BAND_BY, OP_AY, bT, add}};
+        // T* = T^n + (M^y)^{-1} R
+        sp.y1 = {{XR, T, OP_MY, BAND_BY, OP_AY, bT, 1}};
         // S3
         sp.a2 = AsmArgs{2, T, fuel, R, nullptr};
         sp.x2 = {{R, XR, OP_AX, -1, -1, nullptr, 0}};
@@ -130,11 +132,11 @@ iga_status step_impl(const iga_plan *pl, void *T, void *fuel, hipStream_t s, con
     auto sweep = [&](int dir, const std::vector<SweepJob> &j) {
         return launch_sweep(pl, dir, j.data(), (int)j.size(), s);
     };
-    if ((st = launch_assemble(pl, sp.a1.substep, sp.a1.T, sp.a1.fuel, sp.a1.R, sp.a1.RF, s, src0)))
+    if ((st = launch_assemble(pl, sp.a1.substep, sp.a1.T, sp.a1.fuel, sp.a1.R, sp.a1.RF, true, s, src0)))
         return st;
     if ((st = sweep(0, sp.x1)) || (st = sweep(1, sp.y1))) return st;
     if (!sp.two) return IGA_OK;
-    if ((st = launch_assemble(pl, sp.a2.substep, sp.a2.T, sp.a2.fuel, sp.a2.R, sp.a2.RF, s, src1)))
+    if ((st = launch_assemble(pl, sp.a2.substep, sp.a2.T, sp.a2.fuel, sp.a2.R, sp.a2.RF, true, s, src1)))
         return st;
     if ((st = sweep(0, sp.x2)) || (st = sweep(1, sp.y2))) return st;
     return IGA_OK;
@@ -197,8 +199,8 @@ iga_status iga_plan_create(const iga_plan_desc *desc, iga_plan **out)
             delete pl;
             return st;
         }
-        pl->asm_rows = pl->Nx >= 2048 ? 32 : 16;
-        pl->asm_stack = pl->fp32 && pl->P <= 2;
+        pl->asm_rows = default_assembly_rows(pl, assembly_work(pl));
+        pl->asm_stack = 1;
     } catch (const std::bad_alloc &) {
         delete pl;
         return fail(IGA_ENOMEM, "host allocation failed");
@@ -262,7 +264,8 @@ iga_status iga_assemble_rhs(const iga_plan *plan, int32_t substep, const void *T
         return fail(IGA_EINVAL,
                     "Strang substep must be 0 or 2 (the middle substep is iga_line_solve(1, 2))");
     }
-    return launch_assemble(plan, substep, T, fuel, rhs_T, rhs_fuel, static_cast<hipStream_t>(stream));
+    return launch_assemble(plan, substep, T, fuel, rhs_T, rhs_fuel, plan->fp32,
+                           static_cast<hipStream_t>(stream));
 }
 
 iga_status iga_line_solve(const iga_plan *plan, int32_t dir, int32_t which, void *x, void *stream)
@@ -288,7 +291,7 @@ iga_status iga_line_solve(const iga_plan *plan, int32_t dir, int32_t which, void
                                hipMemcpyDeviceToDevice, s));
         return IGA_OK;
     }
-    if (which == 2) j = SweepJob{x, x, -1, B, A, nullptr, plan->delta ? 1 : 0};
+    if (which == 2) j = SweepJob{x, x, -1, B, A, nullptr, 1};
     return launch_sweep(plan, dir, &j, 1, s);
 }
 
@@ -505,7 +508,7 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
                 plan->asm_rows = rows;
                 plan->asm_stack = stack;
                 float ms =
-                    time_launches(s, reps, [&] { return launch_assemble(plan, 0, T, fuel, R, RF, s); });
+                    time_launches(s, reps, [&] { return launch_assemble(plan, 0, T, fuel, R, RF, true, s); });
                 if (ms >= 0) asm_timed.emplace_back(ms, std::make_pair(rows, stack));
                 if (ms >= 0 && ms < best_ms) {
                     best_ms = ms;
@@ -515,11 +518,9 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
             }
         plan->asm_rows = best;
         plan->asm_stack = best_stack;
-        if ((st = launch_assemble(plan, 0, T, fuel, R, RF, s))) return st;
+        if ((st = launch_assemble(plan, 0, T, fuel, R, RF, true, s))) return st;
     }
     // line solves: lines per workgroup, timed on the step's own jobs
-    const void *bT = plan->delta ? T : nullptr;
-    const int add = plan->delta ? 1 : 0;
     auto apply = [&](int dir, const Schedule &sc) {
         if (sc.col) return choose_column_schedule(plan, sc.mm);
         if (sc.win) return choose_window_schedule(plan, dir, sc.lines, sc.mm);
@@ -534,10 +535,10 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
             jobs[1] = SweepJob{RF, out2, OP_MX, -1, -1, nullptr, 0};
             nj = 2;
         } else if (plan->d.scheme == IGA_STRANG_CN) {
-            jobs[0] = SweepJob{R, out.ptr, OP_MY, BAND_BY, OP_AY, bT, add};
+            jobs[0] = SweepJob{R, out.ptr, OP_MY, BAND_BY, OP_AY, T, 1};
             nj = 1;
         } else {
-            jobs[0] = SweepJob{R, out.ptr, OP_MY, -1, -1, bT, 0};
+            jobs[0] = SweepJob{R, out.ptr, OP_MY, -1, -1, T, 0};
             nj = 1;
         }
         const Schedule keep = plan->sched[dir];

@@ -159,11 +159,10 @@ struct iga_plan {
     int P = 2, Nx = 0, Ny = 0;
     size_t ndof = 0;
     bool fp32 = false;
-    bool delta = false;           // increment form (FP32 plans)
     size_t wsize = 8;             // bytes per state element
     iga::DirHost X, Y;
     std::vector<double> op_band[iga::NOPS];    // host FP64 operators
-    std::vector<double> cn_band[iga::NBANDS];  // explicit CN operators (B, or B - A)
+    std::vector<double> cn_band[iga::NBANDS];  // explicit CN operators, B - A
     iga::Schedule sched[2];
     int win_buffers[2] = {0, 0};   // requested windowed LDS form: 0 automatic, 1 or 2 buffers
     int asm_rows = 16;
@@ -180,7 +179,6 @@ struct iga_plan {
     iga::WinGeom wgeom[2];
     iga::DevBuf op_wrows[iga::NOPS], op_wa64[iga::NOPS], band_wrows[iga::NBANDS];
     // assembly tables
-    iga::DevBuf asm_bx, asm_by;                // [e][2][P+1][P+1]  (val, der), state precision
     iga::DevBuf asm_wx, asm_wy;                // wind remainders at x-qps / y-qps
     iga::DevBuf scratch_r, scratch_rf;         // right-hand sides
     iga::DevBuf scratch_r2, scratch_rf2;       // x-solved right-hand sides (column waves)
@@ -211,9 +209,17 @@ iga_status choose_column_schedule(iga_plan *pl, int mm);
 iga_status launch_factor(iga_plan *pl, hipStream_t s);
 
 // kernels (assemble.hip)
+// delta: increment form (R - the implicit operator applied to T), as every
+// step uses; else R itself
 // src: optional source sampled at the quadrature points (forced steps)
 iga_status launch_assemble(const iga_plan *pl, int substep, const void *T, const void *fuel,
-                           void *rhs, void *rhs_fuel, hipStream_t s, const void *src = nullptr);
+                           void *rhs, void *rhs_fuel, bool delta, hipStream_t s,
+                           const void *src = nullptr);
+
+// marched rows of one assembly (strips times dof rows), and the default tile
+// height for a launch of `work` of them (one plan, or all of an ensemble)
+double assembly_work(const iga_plan *pl);
+int default_assembly_rows(const iga_plan *pl, double work);
 
 // kernels (sweep.hip)
 struct SweepJob {

@@ -143,7 +143,6 @@ iga_status build_plan_host(iga_plan *pl)
     pl->Ny = pl->Y.N;
     pl->ndof = (size_t)pl->Nx * pl->Ny;
     pl->fp32 = d.precision == IGA_FP32_REFINE;
-    pl->delta = pl->fp32;
     pl->wsize = pl->fp32 ? 4 : 8;
     for (int dir = 0; dir < 2; ++dir) {
         const DirHost &D = dir ? pl->Y : pl->X;
@@ -155,10 +154,9 @@ iga_status build_plan_host(iga_plan *pl)
         for (size_t k = 0; k < n; ++k) {
             double lin = d.c.c_diff * D.K[k] + d.c.c_adv * bbar * D.G[k];
             A[k] = (1.0 - g * react) * D.M[k] + g * lin;
-            // explicit Crank-Nicolson counterpart B = (1 + g react) M - g (...);
-            // in increment form the line solve applies B - A = 2 g (react M - (...))
-            B[k] = pl->delta ? 2.0 * g * (react * D.M[k] - lin)
-                             : (1.0 + g * react) * D.M[k] - g * lin;
+            // the explicit Crank-Nicolson counterpart is B = (1 + g react) M - g (...);
+            // the line solves apply B - A = 2 g (react M - (...)) and add x
+            B[k] = 2.0 * g * (react * D.M[k] - lin);
         }
         pl->op_band[dir ? OP_AY : OP_AX] = A;
         pl->op_band[dir ? OP_MY : OP_MX] = M;
@@ -190,21 +188,6 @@ static iga_status upload_state(const iga_plan *pl, DevBuf &b, const std::vector<
     return pl->fp32 ? upload_vec<float>(b, v) : upload_vec<double>(b, v);
 }
 
-// Assembly tables of one direction: per element e, [0][a][q] values and
-// [1][a][q] derivatives of the element's p+1 functions at its p+1 points.
-static std::vector<double> asm_table(const DirHost &D, int p)
-{
-    int nq = p + 1;
-    std::vector<double> t((size_t)D.n * 2 * nq * nq);
-    for (int e = 0; e < D.n; ++e)
-        for (int a = 0; a < nq; ++a)
-            for (int q = 0; q < nq; ++q) {
-                t[(((size_t)e * 2 + 0) * nq + a) * nq + q] = D.bv[((size_t)e * nq + a) * nq + q];
-                t[(((size_t)e * 2 + 1) * nq + a) * nq + q] = D.bd[((size_t)e * nq + a) * nq + q];
-            }
-    return t;
-}
-
 iga_status upload_plan(iga_plan *pl)
 {
     const int p = pl->P, nq = p + 1;
@@ -212,7 +195,6 @@ iga_status upload_plan(iga_plan *pl)
     iga_status st;
     for (int op = 0; op < NOPS; ++op)
         if ((st = upload_vec<double>(pl->op_a64[op], pl->op_band[op]))) return st;
-    std::vector<double> tx = asm_table(pl->X, p), ty = asm_table(pl->Y, p);
     // explicit wind remainders: (by(x) - bbar_y) at x-points, (bx(y) - bbar_x) at y-points
     std::vector<double> wx((size_t)pl->X.n * nq), wy((size_t)pl->Y.n * nq);
     const bool sc = d.wind.kind == IGA_WIND_SINCOS;
@@ -228,8 +210,6 @@ iga_status upload_plan(iga_plan *pl)
             double bx = d.wind.bx + (sc ? d.wind.ax * std::sin(2.0 * M_PI * y / d.len_y) : 0.0);
             wy[(size_t)e * nq + q] = bx - d.wind.bbar_x;
         }
-    if ((st = upload_state(pl, pl->asm_bx, tx))) return st;
-    if ((st = upload_state(pl, pl->asm_by, ty))) return st;
     if ((st = upload_state(pl, pl->asm_wx, wx))) return st;
     if ((st = upload_state(pl, pl->asm_wy, wy))) return st;
     IGA_HIP(pl->scratch_r.alloc(pl->ndof * pl->wsize));
