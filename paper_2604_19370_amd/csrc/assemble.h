@@ -13,19 +13,16 @@
 // A forced step adds to f a source sampled at the quadrature points (the
 // forcing of the manufactured-solution study, Section 6.1); that is a
 // separate compile-time variant, the unforced kernels do not test for it.
-// FP32 plans assemble the same quantities in increment form, R - A_impl S
-// (A_impl the substep's implicit Kronecker operator), so that the float
-// right-hand side carries only the O(tau) change of the state.
+// Steps assemble the same quantities in increment form, R - A_impl S (A_impl
+// the substep's implicit Kronecker operator): the right-hand side carries only
+// the O(tau) change of the state, and is exactly zero where nothing happens.
 //
 // Schedule: one wavefront owns a strip of 64 element columns (lane = element
 // column ey, the strip's first p lanes are halo) and marches along x over a
 // tile of element rows.  Per step it takes one new coefficient row of S and
-// fuel (loaded p+1 rows ahead, coalesced), contracts it in y with the lane's
-// own basis table (the y half of the sum factorisation, reused by the p+1
-// elements that share the row; neighbouring columns arrive by DPP rotates),
-// finishes the x half with the element row's basis table (one for the
-// whole wavefront: held in registers across steps, or read from LDS),
-// evaluates the pointwise terms at the (p+1)^2 points and
+// fuel (loaded p+1 rows ahead, coalesced), contracts it in y (the y half of
+// the sum factorisation, reused by the p+1 elements that share the row;
+// neighbouring columns arrive by DPP rotates), finishes the x half, evaluates the pointwise terms at the (p+1)^2 points and
 // accumulates the x half of the test-function contraction into per-row
 // accumulators.  When a dof row is complete its y contraction is gathered from
 // the p neighbouring lanes and stored.  In the stacked variant a workgroup's
@@ -39,14 +36,13 @@
 // runs on every XCD.
 //
 // The marching loop is unrolled by p+1, so the rolling windows (coefficient
-// rows, accumulators, pending loads) are renamed, not copied.  The x
-// quadrature weight is folded into the pointwise coefficients, the y weight
-// into the completed row.  The ignition indicator needs S > T_ig somewhere in
+// rows, accumulators, pending loads) are renamed, not copied.  The quadrature
+// weights are folded into the test functions' values.  The ignition indicator needs S > T_ig somewhere in
 // the element; S is a convex combination of the element's coefficients
 // (B-splines are non-negative and sum to one), so where no coefficient of any
 // element of the wavefront's row exceeds T_ig (less a rounding margin) the
 // Arrhenius term is zero and the fuel terms that only it feeds are skipped.
-// In increment form (FP32 plans) an element whose coefficients all equal the
+// In increment form an element whose coefficients all equal the
 // ambient fixed point (where c_react T + c_forcing - c_rad T^4 = 0) has no
 // gradient and no net source, so it contributes nothing; where that holds for
 // every element of the wavefront's row, the row's pointwise terms and test
@@ -251,12 +247,18 @@ __device__ __forceinline__ void from_uniform(T (&r)[P + 1], int e, int n)
 //   ap:   the same record as a, in constant memory: constants that need not
 //         stay in scalar registers are read from it where they are used
 //
-// Bound by VALU issue.  Per element and step (p = 2): 9 operations for the y
-// half of the new row, 48 for the values and gradient at the points, 90
-// pointwise, 76 for the x half of the test contraction and about 20 for the
-// finished row.  The fuel enters only where the ignition terms are evaluated
-// (LDS accumulators, y contraction formed there), so its cost elsewhere is its
-// loads.  With no tables to hold, p = 2 takes @REGS@.
+// Bound by VALU issue at 4096^2 (S3 in FP32: 9 tenths of its time by instruction
+// count), by latency on small meshes.  Per element and step (p = 2): 9
+// operations for the y half of the new row, 48 for the values and gradient at
+// the points, 90 pointwise, 76 for the x half of the test contraction and about
+// 20 for the finished row.  The fuel enters only where the ignition terms are
+// evaluated (LDS accumulators, y contraction formed there), so its cost
+// elsewhere is its loads.  Against tables per element and column in registers
+// (p = 2: 36 of them), which this replaced: FP32 113-122 registers for 152-168
+// (4 wavefronts per SIMD for 3), double 215-227 for 340 (2 for 1).  Both
+// assemblies of a Strang step, best tiles: FP32 4096^2 155 + 140 -> 109 + 101 us,
+// 1024^2 24.0 + 22.8 -> 19.2 + 17.1, cubic 4096^2 399 + 347 -> 284 + 260; direct
+// form in double 4096^2 578 + 408 -> 415 + 250, cubic 1562 + 946 -> 1527 + 830.
 template <typename T, int P, bool FUEL, bool SRC = false>
 __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParams<T>> *ap,
                                               const int strip, const int X0,

@@ -1,0 +1,51 @@
+"""The assembly evaluates every element in the uniform B-spline basis and
+converts the first and last coefficients and test functions: meshes whose ends
+fall on the edges of strips (64 - p columns) and tiles, elements that are not
+square, every degree, against the oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2604_19370_amd import inputs
+from test_gpu_parity import TOL64, dev, host, per_step_parity, plan_and_oracle, rel, torch
+
+pytestmark = pytest.mark.gpu
+
+
+def scenario(nx, ny, p, scheme, seed):
+    sc = inputs.small_case(seed, nx, ny, p, scheme)
+    return dataclasses.replace(sc, len_x=1.7 * nx, len_y=0.6 * ny)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+@pytest.mark.parametrize("dx,dy", [(0, 0), (1, -1), (9, 0), (4, 1), (6, 64)])
+def test_rhs_at_strip_and_tile_edges(p, dx, dy):
+    """nel_x = 2p+1+dx; nel_y around the last column of the first strip (or
+    the second), and the smallest.  Right-hand sides to the FP64 step tolerance."""
+    nx = 2 * p + 1 + dx
+    for ny in (64 - 2 * p + dy, 2 * p + 1):
+        print(f"rhs {nx}x{ny} p{p}", flush=True)
+        sc = scenario(nx, ny, p, "pr", 40 + dx)
+        pl, od = plan_and_oracle(sc)
+        T = sc.T0 + np.random.default_rng(nx).uniform(0, 600, sc.T0.shape)
+        for substep in (0, 1):
+            Rref, RFref = oracle.assemble(od, substep, T, sc.fuel0, with_fuel=True)
+            t, f = dev(T), dev(sc.fuel0)
+            rr, rf = torch.zeros_like(t), torch.zeros_like(t)
+            pl.assemble_rhs(substep, t, f, rr, rf)
+            assert rel(host(rr), Rref) < TOL64
+            assert rel(host(rf), RFref) < TOL64
+        pl.close()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_step_on_rectangular_elements(p, precision):
+    """Whole steps (increment form, ambient elements skipped) where element
+    edges differ between the directions."""
+    sc = scenario(23, 70, p, "strang", 7)
+    pl, od = plan_and_oracle(sc, precision)
+    per_step_parity(pl, od, sc, 2, precision)
+    pl.close()
