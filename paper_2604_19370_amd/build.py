@@ -30,7 +30,9 @@ SOURCES = ["plan.cpp", "api.cpp", "noalloc.cpp", "ensemble.cpp", "factor.hip", "
            "assemble_f1.hip", "assemble_f2.hip", "assemble_f3.hip", "assemble_d1.hip", "assemble_d2.hip",
            "assemble_d3.hip", "sweep.hip",
            "sweep_f1.hip", "sweep_f2.hip", "sweep_f3.hip", "sweep_d1.hip", "sweep_d2.hip",
-           "sweep_d3.hip", "sweep_col.hip", "sample.hip"]
+           "sweep_d3.hip", "sweep_col.hip", "sweep_line.hip",
+           "sweep_line_f1.hip", "sweep_line_f2.hip", "sweep_line_f3.hip", "sweep_line_d1.hip",
+           "sweep_line_d2.hip", "sweep_line_d3.hip", "sample.hip"]
 
 # The double-precision assembly has more constants than scalar registers: hoisted
 # out of the marching loop they are spilled, so they are formed where they are used.

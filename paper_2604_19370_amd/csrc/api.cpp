@@ -79,15 +79,16 @@ iga_status check_field(const void *p, const char *name)
 // field read per y sweep.  A PR or Strang step is six launches:
 // assembly, x sweep, y sweep, twice; an explicit step is the first three.
 // The x sweeps solve in place, or into second scratch fields under a
-// column-wave x schedule (whose waves read rows around their own chunk).
-// work: NULL for the plan's scratch fields, else four fields (R, R_fuel and,
-// under column waves, their x-solved copies) that replace them.
+// column-wave or line-per-lane x schedule (whose waves read rows around their
+// own chunk); so does Strang's fused y sweep under a line-per-lane y schedule.
+// work: NULL for the plan's scratch fields, else the four fields (R, R_fuel and,
+// out of place, their x-solved copies) that replace them.
 void step_phases(const iga_plan *pl, void *T, void *fuel, StepPhases &sp, void *const *work)
 {
     void *R = work ? work[0] : pl->scratch_r.ptr, *RF = work ? work[1] : pl->scratch_rf.ptr;
-    const bool col = pl->sched[0].col != 0;
-    void *XR = col ? (work ? work[2] : pl->scratch_r2.ptr) : R;
-    void *XRF = col ? (work ? work[3] : pl->scratch_rf2.ptr) : RF;
+    void *R2 = work ? work[2] : pl->scratch_r2.ptr, *RF2 = work ? work[3] : pl->scratch_rf2.ptr;
+    const bool oop = pl->sched[0].col || pl->sched[0].line;
+    void *XR = oop ? R2 : R, *XRF = oop ? RF2 : RF;
     const void *bT = T, *bF = fuel;
     const bool pr = pl->d.scheme == IGA_PR;
     // substep 1 (PR: x implicit; Strang: S1) + the fuel right-hand side
@@ -97,6 +98,7 @@ void step_phases(const iga_plan *pl, void *T, void *fuel, StepPhases &sp, void *
     sp.a1 = AsmArgs{0, T, fuel, R, RF};
     sp.x1 = {{R, XR, OP_AX, -1, -1, nullptr, 0}, {RF, XRF, OP_MX, -1, -1, nullptr, 0, zs}};
     sp.two = true;
+    sp.m.clear();
     if (pl->d.scheme == IGA_EXPLICIT) {
         // (M^x (x) M^y) solves of both right-hand sides, in the same launches
         sp.x1[0].op0 = OP_MX;
@@ -113,6 +115,18 @@ void step_phases(const iga_plan *pl, void *T, void *fuel, StepPhases &sp, void *
     } else {
         // S1's y solve fused with S2: T** = (A^y)^{-1} B^y T* along y, with
         // T* = T^n + (M^y)^{-1} R
+        if (pl->sched[1].line) {
+            // S2 on its own, out of place: T* goes to the field that the x sweep
+            // has read (or the spare one), T** to the one T* was solved from,
+            // and S3 takes the fields that are free by then
+            void *S1 = oop ? R : R2, *S2 = XR, *XB = oop ? RF : R2;
+            sp.y1 = {{XR, S1, OP_MY, -1, -1, bT, 0}};
+            sp.m = {{S1, S2, -1, BAND_BY, OP_AY, nullptr, 1}};
+            sp.a2 = AsmArgs{2, S2, fuel, S1, nullptr};
+            sp.x2 = {{S1, XB, OP_AX, -1, -1, nullptr, 0}};
+            sp.y2 = {{XB, T, OP_MY, -1, -1, S2, 0}, {XRF, fuel, OP_MY, -1, -1, bF, 0, zs}};
+            return;
+        }
         sp.y1 = {{XR, T, OP_MY, BAND_BY, OP_AY, bT, 1}};
         // S3
         sp.a2 = AsmArgs{2, T, fuel, R, nullptr};
@@ -136,6 +150,7 @@ iga_status step_impl(const iga_plan *pl, void *T, void *fuel, hipStream_t s, con
         return st;
     if ((st = sweep(0, sp.x1)) || (st = sweep(1, sp.y1))) return st;
     if (!sp.two) return IGA_OK;
+    if (!sp.m.empty() && (st = sweep(1, sp.m))) return st;
     if ((st = launch_assemble(pl, sp.a2.substep, sp.a2.T, sp.a2.fuel, sp.a2.R, sp.a2.RF, true, s, src1)))
         return st;
     if ((st = sweep(0, sp.x2)) || (st = sweep(1, sp.y2))) return st;
@@ -237,8 +252,11 @@ iga_status iga_factor_1d(iga_plan *plan, void *stream)
     for (int dir = 0; dir < 2; ++dir) {
         if (choose_window_schedule(plan, dir, 0, 0) == IGA_OK) continue;
         (void)hipGetLastError();   // the fallback below is deliberate
-        if ((st = choose_schedule(plan, dir, 0, 0))) return st;
+        if ((st = build_scan_tables(plan, dir)) || (st = choose_schedule(plan, dir, 0, 0))) return st;
     }
+    // and, for the steps, line-per-lane solves on top where they are possible
+    for (int dir = 0; dir < 2; ++dir)
+        if (choose_line_schedule(plan, dir)) (void)hipGetLastError();
     set_error("");
     plan->factored = true;
     plan->graph.reset();
@@ -522,9 +540,11 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
     }
     // line solves: lines per workgroup, timed on the step's own jobs
     auto apply = [&](int dir, const Schedule &sc) {
+        iga_status e;
         if (sc.col) return choose_column_schedule(plan, sc.mm);
-        if (sc.win) return choose_window_schedule(plan, dir, sc.lines, sc.mm);
-        return choose_schedule(plan, dir, sc.lines, sc.wpl);
+        if (sc.win) e = choose_window_schedule(plan, dir, sc.lines, sc.mm);
+        else e = choose_schedule(plan, dir, sc.lines, sc.wpl);
+        return e || !sc.line ? e : choose_line_schedule(plan, dir);
     };
     std::vector<std::pair<float, Schedule>> timed[2];   // every candidate, launched alone
     for (int dir = 0; dir < 2; ++dir) {
@@ -545,15 +565,27 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
         Schedule best = keep;
         float best_ms = 1e30f;
         auto consider = [&] {
-            float ms = time_launches(s, reps, [&] { return launch_sweep(plan, dir, jobs, nj, s); });
+            float ms;
+            if (dir && plan->sched[1].line && plan->d.scheme == IGA_STRANG_CN) {
+                // S1's solve and S2 are two launches
+                const SweepJob y{R, out.ptr, OP_MY, -1, -1, T, 0}, m{out.ptr, out2, -1, BAND_BY, OP_AY, nullptr, 1};
+                ms = time_launches(s, reps, [&] {
+                    iga_status e = launch_sweep(plan, dir, &y, 1, s);
+                    return e ? e : launch_sweep(plan, dir, &m, 1, s);
+                });
+            } else {
+                ms = time_launches(s, reps, [&] { return launch_sweep(plan, dir, jobs, nj, s); });
+            }
             if (ms >= 0) timed[dir].emplace_back(ms, plan->sched[dir]);
             if (ms >= 0 && ms < best_ms) {
                 best_ms = ms;
                 best = plan->sched[dir];
             }
         };
-        // column waves (x-lines, FP32), then windowed solves (where the
-        // operators decay fast enough)
+        // line-per-lane solves on top of the current schedule, column waves
+        // (x-lines, FP32), then windowed solves (where the operators decay
+        // fast enough)
+        if (choose_line_schedule(plan, dir) == IGA_OK) consider();
         if (dir == 0)
             for (int mm : {16, 32})
                 if (choose_column_schedule(plan, mm) == IGA_OK) consider();

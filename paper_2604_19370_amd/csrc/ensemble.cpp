@@ -19,7 +19,7 @@ struct iga_ensemble {
     std::vector<void *> T, F;
     bool bound = false;
     BatchLaunch a1, a2;
-    std::vector<BatchLaunch> x1, y1, x2, y2;
+    std::vector<BatchLaunch> x1, y1, m, x2, y2;
     bool two = false;   // some member has a second assembly and sweep pair
     GraphCache graph;
 
@@ -56,14 +56,18 @@ iga_status bind(iga_ensemble *e, void *const *T, void *const *F)
         return IGA_OK;
     e->unbind();
     std::vector<AsmArgs> a1(n), a2;
-    std::vector<std::vector<SweepJob>> x1(n), y1(n), x2, y2;
-    std::vector<iga_plan *> second;   // members with a second phase
+    std::vector<std::vector<SweepJob>> x1(n), y1(n), mid, x2, y2;
+    std::vector<iga_plan *> second, middle;   // members with a second phase, with S2 on its own
     for (size_t m = 0; m < n; ++m) {
         StepPhases sp;
         step_phases(e->plans[m], T[m], F[m], sp);
         a1[m] = sp.a1;
         x1[m] = sp.x1;
         y1[m] = sp.y1;
+        if (!sp.m.empty()) {
+            middle.push_back(e->plans[m]);
+            mid.push_back(sp.m);
+        }
         if (sp.two) {
             second.push_back(e->plans[m]);
             a2.push_back(sp.a2);
@@ -75,6 +79,8 @@ iga_status bind(iga_ensemble *e, void *const *T, void *const *F)
     if ((st = build_assemble_batch(e->plans, a1, e->a1)) ||
         (st = build_sweep_batch(e->plans, 0, x1, e->x1)) || (st = build_sweep_batch(e->plans, 1, y1, e->y1)))
         return st;
+    e->m.clear();
+    if (!middle.empty() && (st = build_sweep_batch(middle, 1, mid, e->m))) return st;
     e->two = !second.empty();
     if (e->two &&
         ((st = build_assemble_batch(second, a2, e->a2)) || (st = build_sweep_batch(second, 0, x2, e->x2)) ||
@@ -100,6 +106,7 @@ iga_status step_bound(iga_ensemble *e, hipStream_t s)
     iga_status st;
     if ((st = launch_batch(e->a1, s)) || (st = launch_all(e->x1, s)) || (st = launch_all(e->y1, s)))
         return st;
+    if ((st = launch_all(e->m, s))) return st;
     if (e->two &&
         ((st = launch_batch(e->a2, s)) || (st = launch_all(e->x2, s)) || (st = launch_all(e->y2, s))))
         return st;
@@ -156,6 +163,17 @@ iga_status set_window_all(iga_ensemble *e, int dir, int lines, int mm)
     return IGA_OK;
 }
 
+// line-per-lane solves for the steps of every member that allows them
+bool set_line_all(iga_ensemble *e, int dir)
+{
+    bool any = false;
+    for (iga_plan *pl : e->plans) any = choose_line_schedule(pl, dir) == IGA_OK || any;
+    (void)hipGetLastError();
+    set_error("");
+    e->unbind();
+    return any;
+}
+
 // schedule groups of direction dir among all members (second = false) or
 // among the members with a second assembly and sweep pair (second = true)
 int groups(const iga_ensemble *e, int dir, bool second = false)
@@ -166,7 +184,8 @@ int groups(const iga_ensemble *e, int dir, bool second = false)
         const Schedule &s = pl->sched[dir];
         bool found = false;
         for (const Schedule &t : seen)
-            found = found || (t.mm == s.mm && t.lines * t.wpl == s.lines * s.wpl && t.win == s.win);
+            found = found || (t.line == s.line &&
+                              (s.line || (t.mm == s.mm && t.lines * t.wpl == s.lines * s.wpl && t.win == s.win)));
         if (!found) seen.push_back(s);
     }
     return (int)seen.size();
@@ -211,6 +230,7 @@ iga_status iga_ensemble_create(const iga_plan_desc *members, int32_t n, iga_ense
         delete e;
         return st;
     }
+    for (int dir = 0; dir < 2; ++dir) set_line_all(e, dir);
     *out = e;
     return IGA_OK;
 }
@@ -232,7 +252,10 @@ iga_status iga_ensemble_launches(const iga_ensemble *ens, int32_t *per_step)
 {
     if (!ens || !per_step) return fail(IGA_EINVAL, "NULL argument");
     const int g2 = groups(ens, 0, true) + groups(ens, 1, true);
-    *per_step = 1 + groups(ens, 0) + groups(ens, 1) + (g2 ? 1 + g2 : 0);
+    bool middle = false;   // S2 of line-per-lane members: one more launch
+    for (const iga_plan *pl : ens->plans)
+        middle = middle || (pl->sched[1].line && pl->d.scheme == IGA_STRANG_CN);
+    *per_step = 1 + groups(ens, 0) + groups(ens, 1) + (middle ? 1 : 0) + (g2 ? 1 + g2 : 0);
     return IGA_OK;
 }
 
@@ -281,6 +304,7 @@ iga_status iga_ensemble_set_schedule(iga_ensemble *ens, int32_t dir, int32_t lin
         for (size_t m = 0; m < ens->plans.size(); ++m) {
             if (keep[m].win) (void)choose_window_schedule(ens->plans[m], dir, keep[m].lines, keep[m].mm);
             else (void)choose_schedule(ens->plans[m], dir, keep[m].lines, keep[m].wpl);
+            if (keep[m].line) (void)choose_line_schedule(ens->plans[m], dir);
         }
         ens->unbind();
     }
@@ -301,6 +325,7 @@ iga_status iga_ensemble_set_window_schedule(iga_ensemble *ens, int32_t dir, int3
         for (size_t m = 0; m < ens->plans.size(); ++m) {
             if (keep[m].win) (void)choose_window_schedule(ens->plans[m], dir, keep[m].lines, keep[m].mm);
             else (void)choose_schedule(ens->plans[m], dir, keep[m].lines, keep[m].wpl);
+            if (keep[m].line) (void)choose_line_schedule(ens->plans[m], dir);
         }
         ens->unbind();
     }
@@ -360,29 +385,44 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
     // step's own jobs (fused Crank-Nicolson solves, base states, zero skips),
     // every state field replaced by a scratch buffer of the member: the
     // caller's fields are not written
+    auto spare_field = [](const iga_plan *pl) { return (pl->ndof * pl->wsize + 255) & ~size_t(255); };
+    std::vector<DevBuf> spare(n);   // in the place of every member's (T, fuel)
+    for (size_t m = 0; m < n; ++m) {
+        const iga_plan *pl = ens->plans[m];
+        IGA_HIP(spare[m].alloc(2 * spare_field(pl)));
+        char *p = spare[m].as<char>();
+        IGA_HIP(hipMemcpyAsync(p, T[m], pl->ndof * pl->wsize, hipMemcpyDeviceToDevice, s));
+        IGA_HIP(hipMemcpyAsync(p + spare_field(pl), fuel[m], pl->ndof * pl->wsize, hipMemcpyDeviceToDevice, s));
+    }
     for (int dir = 0; dir < 2; ++dir) {
-        std::vector<iga_plan *> second;
-        std::vector<std::vector<SweepJob>> ja(n), jb;
-        for (size_t m = 0; m < n; ++m) {
-            iga_plan *pl = ens->plans[m];
-            const bool r2 = pl->scratch_r2.ptr != nullptr;   // FP32 plans
-            StepPhases sp;
-            step_phases(pl, r2 ? pl->scratch_r2.ptr : pl->scratch_r.ptr,
-                        r2 ? pl->scratch_rf2.ptr : pl->scratch_rf.ptr, sp);
-            ja[m] = dir == 0 ? sp.x1 : sp.y1;
-            if (sp.two) {
-                second.push_back(pl);
-                jb.push_back(dir == 0 ? sp.x2 : sp.y2);
-            }
-        }
         int best_l = 0, best_w = 0, best_win = 0;
         float best_ms = 1e30f;
         auto consider = [&](int lines, int w, int win) {
-            std::vector<BatchLaunch> bla, blb;
+            // the step's own jobs under this schedule (their fields depend on it)
+            std::vector<iga_plan *> second;
+            std::vector<iga_plan *> middle;
+            std::vector<std::vector<SweepJob>> ja(n), jb, jm;
+            for (size_t m = 0; m < n; ++m) {
+                iga_plan *pl = ens->plans[m];
+                StepPhases sp;
+                step_phases(pl, spare[m].ptr, spare[m].as<char>() + spare_field(pl), sp);
+                ja[m] = dir == 0 ? sp.x1 : sp.y1;
+                if (dir && !sp.m.empty()) {
+                    middle.push_back(pl);
+                    jm.push_back(sp.m);
+                }
+                if (sp.two) {
+                    second.push_back(pl);
+                    jb.push_back(dir == 0 ? sp.x2 : sp.y2);
+                }
+            }
+            std::vector<BatchLaunch> bla, blb, blm;
             if (build_sweep_batch(ens->plans, dir, ja, bla) != IGA_OK) return;
             if (!second.empty() && build_sweep_batch(second, dir, jb, blb) != IGA_OK) return;
+            if (!middle.empty() && build_sweep_batch(middle, dir, jm, blm) != IGA_OK) return;
             float ms = time_launches(s, reps, [&] {
                 iga_status e = launch_all(bla, s);
+                if (!e) e = launch_all(blm, s);
                 return e ? e : launch_all(blb, s);
             });
             if (ms >= 0 && ms < best_ms) {
@@ -392,6 +432,7 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
                 best_win = win;
             }
         };
+        if (set_line_all(ens, dir)) consider(1, 0, 2);
         for (int mm : {9, 13, 17, 25, 33})
             for (int lines : {1, 2, 4, 8, 16})
                 if (set_window_all(ens, dir, lines, mm) == IGA_OK) consider(lines, mm, 1);
@@ -403,6 +444,11 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
             }
         }
         if (!best_l) return fail(IGA_EUNSUPPORTED, "no line-solve schedule fits every member");
+        if (best_win == 2) {
+            if ((st = set_window_all(ens, dir, dir ? 2 : 4, 17))) return st;
+            (void)set_line_all(ens, dir);
+            continue;
+        }
         if ((st = best_win ? set_window_all(ens, dir, best_l, best_w)
                            : set_schedule_all(ens, dir, best_l, best_w)))
             return st;

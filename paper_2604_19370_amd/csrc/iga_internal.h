@@ -82,6 +82,9 @@ struct Schedule {
     int win = 0;   // 1: windowed solves (see WinGeom), 0: exact chunk scan
     int col = 0;   // 1 (x-lines, FP32): column waves, mm rows per chunk (sweep_col.h)
     int compact = 0;   // windowed: one line buffer per line (see WSweepParams)
+    // 1: the steps use the line-per-lane solves (sweep_line.h) in place of the
+    // above; iga_line_solve, in place, does not
+    int line = 0;
 };
 
 // Windowed line solves (truncated partition): each lane restarts forward and
@@ -100,6 +103,13 @@ struct WinGeom {
     int nhead = 0, tail0 = 0, tail1 = 0;
     int off_head = 0, off_tail = 0, off_canon = 0, off_id = 0, nrows = 0;
     int aoff_head = 0, aoff_tail = 0, aoff_canon = 0, aoff_id = 0, anrows = 0;
+};
+
+// Line-per-lane solves of one direction (LineParams): tiles [0, lo) and
+// [hi, ..) use the edge rows, line rows [0, K0) and [NK, N).
+struct LineGeom {
+    int lo = 0, hi = 0, K0 = 0, NK = 0, nrows = 0;
+    size_t off[5] = {0, 0, 0, 0, 0};   // in line_tab: rows and meet of A, of M, rows of D
 };
 
 // Compressed coefficient tables of one banded operator (host copy).  Rows
@@ -186,6 +196,11 @@ struct iga_plan {
     // size (ColEdge in sweep_col.h) and the edge chunks [0, col_lo), [col_hi, ..)
     iga::DevBuf col_edge_f[iga::NOPS], col_edge_d[iga::NOPS];
     int col_lo = 0, col_hi = 0;
+    // line-per-lane solves: the tables of each direction, and the canonical
+    // constants of the operators and of D = B - A along y
+    iga::DevBuf line_tab[2];
+    std::vector<double> line_const[iga::NOPS], line_d;
+    iga::LineGeom line_geom[2];
     iga::DevBuf flag;                          // non-finite detector
     bool factored = false;
     iga::GraphCache graph;
@@ -204,6 +219,11 @@ WinGeom window_geometry(const iga_plan *pl, int dir, int mm, int wpl);
 iga_status build_window_tables(iga_plan *pl, int dir);
 iga_status choose_window_schedule(iga_plan *pl, int dir, int lines, int mm);
 iga_status choose_column_schedule(iga_plan *pl, int mm);
+// helpers of the table builders (plan.cpp)
+int row_of(int r, int K0, int NK, int nrows);
+void interior_range(const std::vector<double> &f, int N, int RS, double rtol, int &K0, int &NK);
+std::vector<double> compress_rows(const std::vector<double> &f, int N, int RS, int K0, int NK);
+int compute_warmup(const OpHost &o, int N, int P, double tol, int hmax);
 
 // kernels (factor.hip)
 iga_status launch_factor(iga_plan *pl, hipStream_t s);
@@ -243,6 +263,13 @@ bool csweep_ok(const iga_plan *pl);
 bool csweep_rows_ok(int mm);
 iga_status launch_csweep(const iga_plan *pl, const SweepJob *jobs, int njobs, hipStream_t s);
 iga_status build_column_edges(iga_plan *pl, int mm);   // edge windows for chunks of mm rows
+// line-per-lane solves (sweep_line.hip), out of place
+iga_status choose_line_schedule(iga_plan *pl, int dir);
+bool line_jobs_ok(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs);
+iga_status launch_line(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs, hipStream_t s);
+struct BatchLaunch;
+iga_status build_line_batch(const std::vector<iga_plan *> &pls, const std::vector<int> &who, int dir,
+                            const std::vector<std::vector<SweepJob>> &jobs, BatchLaunch &out);
 int sweep_capacity(int m);           // smallest compiled register capacity >= m (0: none)
 
 // A prepared batched launch over ensemble members: kernel, per-member
@@ -285,7 +312,7 @@ iga_status launch_nonfinite(const iga_plan *pl, const void *T, const void *fuel,
 // the launches of one step of a plan on fields (T, fuel) (api.cpp)
 struct StepPhases {
     AsmArgs a1, a2;
-    std::vector<SweepJob> x1, y1, x2, y2;
+    std::vector<SweepJob> x1, y1, m, x2, y2;   // m: Strang's middle substep, unless fused into y1
     bool two = true;   // false: the step is a1, x1, y1 only (explicit scheme)
 };
 void step_phases(const iga_plan *pl, void *T, void *fuel, StepPhases &sp,

@@ -14,11 +14,13 @@
 
 namespace {
 
-// Right-hand sides of one step: 2 fields (4 under column-wave x sweeps).
+// Right-hand sides of one step that a plan may need: 2 fields (4 under
+// column-wave x sweeps).
 constexpr size_t SCRATCH_BYTES = size_t(64) << 20;   // IGA_NOALLOC_SCRATCH_BYTES
 static_assert(SCRATCH_BYTES == IGA_NOALLOC_SCRATCH_BYTES, "header and source disagree");
 
-static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
+// Out-of-place sweeps take four fields of any plan whose two fit.
+static __device__ __align__(256) unsigned char scratch[2 * SCRATCH_BYTES];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_lock;

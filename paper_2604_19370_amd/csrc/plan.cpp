@@ -98,7 +98,8 @@ static void build_dir(DirHost &D, int n, int p, double L)
     // rows of M, K, G are exactly Toeplitz) with no cancellation at large x.
     std::vector<double> tl(n + 2 * p + 1);
     for (int e = 0; e < n; ++e) {
-        for (int k = 0; k < n + 2 * p + 1; ++k)
+        // the knots that the element's functions use
+        for (int k = e; k < std::min(e + 2 * p + 2, n + 2 * p + 1); ++k)
             tl[k] = (double)(std::min(std::max(k - p, 0), n) - e) * D.h;
         for (int q = 0; q < nq; ++q) {
             const double xl = 0.5 * (gx[q] + 1.0) * D.h;
@@ -233,7 +234,7 @@ iga_status upload_plan(iga_plan *pl)
 // ---------------------------------------------------------------------------
 // Rows of `f` (stride RS, N rows) that agree with the middle row to `rtol`
 // form the interior [K0, NK).
-static void interior_range(const std::vector<double> &f, int N, int RS, double rtol, int &K0,
+void interior_range(const std::vector<double> &f, int N, int RS, double rtol, int &K0,
                            int &NK)
 {
     const int mid = N / 2;
@@ -252,7 +253,7 @@ static void interior_range(const std::vector<double> &f, int N, int RS, double r
         if (!same(r)) { NK = r; break; }
 }
 
-static std::vector<double> compress_rows(const std::vector<double> &f, int N, int RS, int K0, int NK)
+std::vector<double> compress_rows(const std::vector<double> &f, int N, int RS, int K0, int NK)
 {
     std::vector<double> out;
     out.reserve((size_t)(K0 + 1 + N - NK) * RS);
@@ -265,7 +266,7 @@ static std::vector<double> compress_rows(const std::vector<double> &f, int N, in
 
 // table row of line row r (the kernels' mapping): rows below K0 and from NK
 // on are stored, the interior shares row K0, padding rows map to the last row
-static inline int row_of(int r, int K0, int NK, int nrows)
+int row_of(int r, int K0, int NK, int nrows)
 {
     return std::min(std::min(r, K0) + std::max(0, r - NK + 1), nrows - 1);
 }
@@ -341,7 +342,7 @@ iga_status build_scan_tables(iga_plan *pl, int dir)
 // such matrices applied to the true state.  The warm-up is the smallest h
 // whose products from every start (head rows, the canonical interior, tail
 // rows) have infinity norm <= tol; 0 if none up to hmax.
-static int compute_warmup(const OpHost &o, int N, int P, double tol, int hmax)
+int compute_warmup(const OpHost &o, int N, int P, double tol, int hmax)
 {
     const int RS = 2 * P + 2;
     auto row = [&](int r) { return &o.rows[(size_t)row_of(r, o.K0, o.NK, o.nrows) * RS]; };
@@ -586,8 +587,6 @@ iga_status build_solve_tables(iga_plan *pl)
         o.H = compute_warmup(o, N, P, pl->fp32 ? std::ldexp(1.0, -20) : std::ldexp(1.0, -55), 96);
         o.Hc = pl->fp32 ? compute_warmup(o, N, P, std::ldexp(1.0, -12), 96) : o.H;
     }
-    for (int dir = 0; dir < 2; ++dir)
-        if ((st = build_scan_tables(pl, dir))) return st;
     for (int b = 0; b < NBANDS; ++b) {
         const int N = b == BAND_BX ? pl->Nx : pl->Ny;
         std::vector<double> a((size_t)N * RS, 0.0);
@@ -626,6 +625,7 @@ iga_status choose_schedule(iga_plan *pl, int dir, int lines, int wpl)
     sc.wpl = wpl;
     sc.win = 0;
     sc.col = 0;
+    sc.line = 0;
     const int maxw = (!pl->fp32 && pl->P == 3 && mm >= 12) ? 8 : 16;   // wavefronts per workgroup
     if (lines <= 0) {
         // widest workgroup (<= 16 wavefronts) that fits LDS and still gives
@@ -695,6 +695,7 @@ iga_status choose_window_schedule(iga_plan *pl, int dir, int lines, int mm)
     sc.mm = mm;
     sc.win = 1;
     sc.col = 0;
+    sc.line = 0;
     iga_status st = build_window_tables(pl, dir);
     if (!st) st = wsweep_prepare(pl, dir);
     if (st) {
@@ -724,6 +725,7 @@ iga_status choose_column_schedule(iga_plan *pl, int mm)
     sc.mm = mm;
     sc.win = 0;
     sc.col = 1;
+    sc.line = 0;
     return IGA_OK;
 }
 

@@ -237,6 +237,7 @@ static iga_status build_wparams(const iga_plan *pl, int dir, const SweepJob *job
 iga_status launch_sweep(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs, hipStream_t s)
 {
     const Schedule &sc = pl->sched[dir];
+    if (line_jobs_ok(pl, dir, jobs, njobs)) return launch_line(pl, dir, jobs, njobs, s);
     if (sc.col) {
         if (dir != 0) return fail(IGA_EINVAL, "column-wave schedules are for x-lines");
         return launch_csweep(pl, jobs, njobs, s);
@@ -281,6 +282,19 @@ iga_status build_sweep_batch(const std::vector<iga_plan *> &pls, int dir,
         if (done[m0]) continue;
         const Schedule key = pls[m0]->sched[dir];
         if (key.col) return fail(IGA_EUNSUPPORTED, "column-wave schedules are not batched");
+        auto line = [&](size_t m) { return line_jobs_ok(pls[m], dir, jobs[m].data(), (int)jobs[m].size()); };
+        if (line(m0)) {
+            std::vector<int> who;
+            for (size_t m = m0; m < pls.size(); ++m) {
+                if (done[m] || !line(m) || pls[m]->sched[dir].line != key.line) continue;
+                done[m] = 1;
+                who.push_back((int)m);
+            }
+            out.emplace_back();
+            iga_status st = build_line_batch(pls, who, dir, jobs, out.back());
+            if (st) return st;
+            continue;
+        }
         std::vector<SweepParams> prms;
         std::vector<WSweepParams> wprms;
         std::vector<int2> info;
@@ -291,7 +305,7 @@ iga_status build_sweep_batch(const std::vector<iga_plan *> &pls, int dir,
             // one launch per workgroup shape: members whose lines need fewer
             // wavefronts join with proportionally more lines per workgroup
             if (done[m] || sc.mm != key.mm || sc.lines * sc.wpl != key.lines * key.wpl ||
-                sc.win != key.win || (key.win && sc.compact != key.compact))
+                sc.win != key.win || (key.win && sc.compact != key.compact) || line(m))
                 continue;
             done[m] = 1;
             int nlines, njobs;
