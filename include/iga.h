@@ -303,8 +303,9 @@ iga_status iga_plan_solver(const iga_plan *plan, int32_t dir, int32_t *windowed,
  * re-evaluates the p elements above it; the rows where two of its tiles meet
  * are summed in two parts through LDS (deterministic).  Unstacked (0): every
  * tile re-evaluates its own p halo elements, and the wavefronts never wait
- * for each other.  Defaults: stacked, 4 rows on small meshes and more with
- * the mesh (of an ensemble, all its meshes); iga_autotune times both kinds.
+ * for each other.  Defaults: p + 1 rows on small meshes and more with the
+ * mesh (of an ensemble, all its meshes), stacked except on the largest meshes;
+ * iga_autotune times both kinds.
  * stacked must be 0 or 1 (IGA_EINVAL). */
 iga_status iga_plan_set_assembly_rows(iga_plan *plan, int32_t rows);
 int32_t iga_plan_assembly_rows(const iga_plan *plan);

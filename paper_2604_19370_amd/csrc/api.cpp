@@ -215,7 +215,7 @@ iga_status iga_plan_create(const iga_plan_desc *desc, iga_plan **out)
             return st;
         }
         pl->asm_rows = default_assembly_rows(pl, assembly_work(pl));
-        pl->asm_stack = 1;
+        pl->asm_stack = default_assembly_stacking(assembly_work(pl));
     } catch (const std::bad_alloc &) {
         delete pl;
         return fail(IGA_ENOMEM, "host allocation failed");

@@ -19,10 +19,11 @@
 //
 // Schedule: one wavefront owns a strip of 64 element columns (lane = element
 // column ey, the strip's first p lanes are halo) and marches along x over a
-// tile of element rows.  Per step it takes one new coefficient row of S and
-// fuel (loaded p+1 rows ahead, coalesced), contracts it in y (the y half of
-// the sum factorisation, reused by the p+1 elements that share the row;
-// neighbouring columns arrive by DPP rotates), finishes the x half, evaluates the pointwise terms at the (p+1)^2 points and
+// tile of element rows.  Per step it takes one new coefficient row of S
+// (loaded p+1 rows ahead, coalesced; the fuel's rows only where elements are
+// hot), contracts it in y (the y half of the sum factorisation, reused by the
+// p+1 elements that share the row; neighbouring columns arrive by DPP rotates),
+// finishes the x half, evaluates the pointwise terms at the (p+1)^2 points and
 // accumulates the x half of the test-function contraction into per-row
 // accumulators.  When a dof row is complete its y contraction is gathered from
 // the p neighbouring lanes and stored.  In the stacked variant a workgroup's
@@ -252,8 +253,12 @@ __device__ __forceinline__ void from_uniform(T (&r)[P + 1], int e, int n)
 // operations for the y half of the new row, 48 for the values and gradient at
 // the points, 90 pointwise, 76 for the x half of the test contraction and about
 // 20 for the finished row.  The fuel enters only where the ignition terms are
-// evaluated (LDS accumulators, y contraction formed there), so its cost
-// elsewhere is its loads.  Against tables per element and column in registers
+// evaluated (LDS accumulators, y contraction formed there), and its rows are
+// requested only there: loaded ahead with every row of S they cost a quarter of
+// the launch's reads and 8 registers (unstacked steps: 4096^2 FP32 465 -> 454 us,
+// together with the points' exponentials side by side 1500^2 cubic in double
+// 422 -> 400).  Constants of the points in vector registers (double, p <= 2):
+// 4096^2 1126 -> 1116 us a step.  Against tables per element and column in registers
 // (p = 2: 36 of them), which this replaced: FP32 113-122 registers for 152-168
 // (4 wavefronts per SIMD for 3), double 215-227 for 340 (2 for 1).  Both
 // assemblies of a Strang step, best tiles: FP32 4096^2 155 + 140 -> 109 + 101 us,
@@ -290,14 +295,10 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
     const int rlast = min(X1, a.nel_x) + P - 1;
     const unsigned offA = (unsigned)min(max(colA, 0), Ny - 1) * (unsigned)sizeof(T);
     const unsigned offB = okB ? (unsigned)colB * (unsigned)sizeof(T) : offA;
-    auto fetch = [&](int row, T &c0, T &c1, T &f0, T &f1) {
-        const size_t rb = (size_t)min(row, rlast) * Ny * sizeof(T);
-        const char *sr = reinterpret_cast<const char *>(a.S) + rb;
-        const char *fr = reinterpret_cast<const char *>(a.F) + rb;
-        c0 = *reinterpret_cast<const T *>(sr + offA);
-        f0 = *reinterpret_cast<const T *>(fr + offA);
-        c1 = *reinterpret_cast<const T *>(sr + offB);
-        f1 = *reinterpret_cast<const T *>(fr + offB);
+    auto fetch = [&](const T *field, int row, T &c0, T &c1) {
+        const char *p = reinterpret_cast<const char *>(field) + (size_t)min(row, rlast) * Ny * sizeof(T);
+        c0 = *reinterpret_cast<const T *>(p + offA);
+        c1 = *reinterpret_cast<const T *>(p + offB);
     };
     // the p+1 coefficients of the lane's element in one row
     auto element_row = [&](T c0, T c1, T(&cb)[Q]) {
@@ -332,10 +333,15 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
     const int K = X1 - E0 + (tail ? P : 0);   // marching steps
     // rings indexed by (step + i) mod Q
     T tv[Q][Q], td[Q][Q], rmx[Q];
-    T rf0[Q], rf1[Q];   // raw fuel coefficients
+    // raw fuel coefficients, followed while elements are hot: fuel says whether
+    // this step's rows are here (pf: the newest).  The first rows of a tile are
+    // requested in any case: a tile that is hot from its first step would wait
+    // for them
+    T rf0[Q], rf1[Q], pf0, pf1;
+    bool fuel = true;
     bool ram[Q];
     T acc0[Q][Q], acc1[Q][Q];
-    T pc0[Q], pc1[Q], pf0[Q], pf1[Q];
+    T pc0[Q], pc1[Q];
     // live[s]: the dof row in slot s has received the contribution of an
     // evaluated element (wavefront-uniform); a row without one is exactly zero.
     // burnt[s]: the same for its fuel accumulators
@@ -351,9 +357,12 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
     // window rows are transformed, so that their latencies overlap
     T wc0[P], wc1[P];
 #pragma unroll
-    for (int s = 0; s < P; ++s) fetch(E0 + s, wc0[s], wc1[s], rf0[s], rf1[s]);
+    for (int s = 0; s < P; ++s) fetch(a.S, E0 + s, wc0[s], wc1[s]);
 #pragma unroll
-    for (int s = 0; s < Q; ++s) fetch(E0 + P + s, pc0[s], pc1[s], pf0[s], pf1[s]);
+    for (int s = 0; s < Q; ++s) fetch(a.S, E0 + P + s, pc0[s], pc1[s]);
+#pragma unroll
+    for (int s = 0; s < P; ++s) fetch(a.F, E0 + s, rf0[s], rf1[s]);
+    fetch(a.F, E0 + P, pf0, pf1);
     rf0[P] = rf1[P] = T(0);
 #pragma unroll
     for (int s = 0; s < P; ++s) ytransform(wc0[s], wc1[s], tv[s], td[s], rmx[s], ram[s]);
@@ -368,8 +377,6 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
             tv[i][q] = ca * tv[i][q] + cb * tv[j][q] + cc * tv[k][q];
             td[i][q] = ca * td[i][q] + cb * td[j][q] + cc * td[k][q];
         }
-        rf0[i] = ca * rf0[i] + cb * rf0[j] + cc * rf0[k];
-        rf1[i] = ca * rf1[i] + cb * rf1[j] + cc * rf1[k];
     };
     if constexpr (P == 2) {
         if (E0 == 0) mix_rows(0, T(2), 1, T(-1), 1, T(0));
@@ -405,15 +412,30 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
     };
 
     const T t_skip = a.t_skip;
-    auto step = [&](auto phase, int k) {
+    // Constants of the points.  Double: beside the basis values they do not fit
+    // the scalar registers (40 to 300 were spilled into vector lanes); p <= 2
+    // has vector registers left within its occupancy, p = 3 has not and reads
+    // them every step.
+    struct Point {
+        T rad, cs, frc, nldx, nldy, dx, dy, bcay, cy;
+    };
+    auto point_constants = [](CT<AsmParams<T>> *cp) {
+        return Point{cp->rad, cp->cs, cp->frc, cp->nldx, cp->nldy, cp->dx, cp->dy, cp->bcay, cp->cy};
+    };
+    constexpr bool held = sizeof(T) == 8 && P < 3;
+    Point kheld = point_constants(ap);
+    if constexpr (held)
+        asm volatile("" : "+v"(kheld.rad), "+v"(kheld.cs), "+v"(kheld.frc), "+v"(kheld.nldx), "+v"(kheld.nldy),
+                          "+v"(kheld.dx), "+v"(kheld.dy), "+v"(kheld.bcay), "+v"(kheld.cy));
+    auto step = [&](auto phase, int n) {
         constexpr int ph = decltype(phase)::value;
         constexpr int snew = (ph + P) % Q;   // slot of the new coefficient row / dof row ex+P
         constexpr int sp1 = (ph + P + Q - 1) % Q, sp2 = (ph + P + 2 * Q - 2) % Q;   // rows ex+P-1, ex+P-2
-        const int ex = E0 + k;
+        const int ex = E0 + n;
         ytransform(pc0[ph], pc1[ph], tv[snew], td[snew], rmx[snew], ram[snew]);
-        rf0[snew] = pf0[ph];
-        rf1[snew] = pf1[ph];
-        fetch(ex + P + Q, pc0[ph], pc1[ph], pf0[ph], pf1[ph]);
+        rf0[snew] = pf0;
+        rf1[snew] = pf1;
+        fetch(a.S, ex + P + Q, pc0[ph], pc1[ph]);
         if constexpr (P == 2) {
             if (ex == a.nel_x - 1) mix_rows(snew, T(2), sp1, T(-1), sp1, T(0));
         }
@@ -430,20 +452,24 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
         const bool quiet = !SRC && a.amb && __all(!eyok || eam);
         burnt[snew] = false;
         if (ex < a.nel_x && ex < X1 && !quiet) {
-            // double: the constants of all points would not fit the scalar
-            // registers beside the basis values, and are read every step
-            // (held, 40 to 300 of them were spilled into vector lanes)
             CT<AsmParams<T>> *cp = ap;
             if constexpr (sizeof(T) == 8) asm volatile("" : "+s"(cp));
-            const T rad = cp->rad, cs = cp->cs, frc = cp->frc, nldx = cp->nldx, nldy = cp->nldy,
-                    dx = cp->dx, dy = cp->dy;
+            const Point k = held ? kheld : point_constants(cp);
             T ky[Q];
 #pragma unroll
-            for (int q = 0; q < Q; ++q) ky[q] = cp->bcay * as_const(a.wx)[(size_t)ex * Q + q] + cp->cy;
+            for (int q = 0; q < Q; ++q) ky[q] = k.bcay * as_const(a.wx)[(size_t)ex * Q + q] + k.cy;
             T emx = rmx[0];
 #pragma unroll
             for (int s = 1; s < Q; ++s) emx = rmx[s] > emx ? rmx[s] : emx;
             const bool hot = (FUEL && a.fuel_all) || __any(emx > t_skip);
+            if (hot) {
+                if (!fuel) {   // (used after the terms below)
+#pragma unroll
+                    for (int i = 0; i < Q; ++i) fetch(a.F, ex + i, rf0[(ph + i) % Q], rf1[(ph + i) % Q]);
+                }
+                fetch(a.F, ex + P + 1, pf0, pf1);
+            }
+            fuel = hot;
             // linear, loss, forcing, wind and T^3-diffusion terms; the first
             // contribution to the fresh dof row (slot snew) is assigned
 #pragma unroll
@@ -460,7 +486,7 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
                 for (int qx = 0; qx < Q; ++qx) {
                     // chains ordered so that no instruction reads two scalar operands
                     const T s = S[qx], s3 = s * s * s;
-                    T a0 = (rad * s3 + cs) * s + frc;
+                    T a0 = (k.rad * s3 + k.cs) * s + k.frc;
                     a0 += kx[qy] * Sx[qx];
                     a0 += ky[qx] * Sy[qx];
                     if constexpr (SRC) {
@@ -468,8 +494,8 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
                             a0 += a.src_w * a.src[((size_t)ex * Q + qx) * ((size_t)a.nel_y * Q) +
                                                   (size_t)ey * Q + qy];
                     }
-                    const T ax = (nldx * s3 + dx) * Sx[qx];
-                    const T ay = (nldy * s3 + dy) * Sy[qx];
+                    const T ax = (k.nldx * s3 + k.dx) * Sx[qx];
+                    const T ay = (k.nldy * s3 + k.dy) * Sy[qx];
 #pragma unroll
                     for (int i = 0; i < Q; ++i) {
                         const int si = (ph + i) % Q;
@@ -492,12 +518,24 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
                 asm volatile("" : "+s"(hp));
                 const T t_ig = hp->t_ig, fthr = hp->fthr, t_act = hp->t_act, ign = hp->ign,
                         cff = hp->cf, rate = hp->rate;
-                T fb[Q][Q];   // fuel coefficients of the element, by ring row
+                T fb[Q][Q];   // fuel coefficients of the element's rows
+                {
+                    T f0[Q], f1[Q];
 #pragma unroll
-                for (int s = 0; s < Q; ++s) element_row(rf0[s], rf1[s], fb[s]);
+                    for (int i = 0; i < Q; ++i) {
+                        f0[i] = rf0[(ph + i) % Q];
+                        f1[i] = rf1[(ph + i) % Q];
+                    }
+                    if (P > 1 && (ex < P || ex >= a.nel_x - P)) {
+                        to_uniform<T, P>(f0, ex, a.nel_x);
+                        to_uniform<T, P>(f1, ex, a.nel_x);
+                    }
+#pragma unroll
+                    for (int i = 0; i < Q; ++i) element_row(f0[i], f1[i], fb[i]);
+                }
 #pragma unroll
                 for (int qy = 0; qy < Q; ++qy) {
-                    T cv[Q], cf[Q], S[Q], F[Q], un[Q], fa[Q];
+                    T cv[Q], cf[Q], S[Q], F[Q], arr[Q], un[Q], fa[Q];
 #pragma unroll
                     for (int i = 0; i < Q; ++i) {
                         const int si = (ph + i) % Q;
@@ -505,19 +543,32 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
                         cf[i] = T(0);
 #pragma unroll
                         for (int b = 0; b < Q; ++b)
-                            cf[i] += fb[si][b] * T(bval(P, b, gauss_t(Q, qy)));
+                            cf[i] += fb[i][b] * T(bval(P, b, gauss_t(Q, qy)));
                         if (FUEL) fa[i] = burnt[si] ? fuel_at(si, qy) : T(0);
                     }
                     element_values(cv, S, un);
+                    bool lit = false;
 #pragma unroll
                     for (int qx = 0; qx < Q; ++qx) {
                         F[qx] = T(0);
 #pragma unroll
                         for (int i = 0; i < Q; ++i) F[qx] += T(bval(P, i, gauss_t(Q, qx))) * cf[i];
-                        T arr = T(0);
-                        if (S[qx] > t_ig && F[qx] > fthr) arr = S[qx] * exp(-t_act / S[qx]);
-                        const T a0 = ign * arr;
-                        const T af = F[qx] * (cff - rate * arr);
+                        arr[qx] = T(0);
+                        lit = lit | ((S[qx] > t_ig) & (F[qx] > fthr));
+                    }
+                    // the points side by side: their chains (division,
+                    // exponential) are far longer than they are wide
+                    if (__any(lit)) {
+#pragma unroll
+                        for (int qx = 0; qx < Q; ++qx) {
+                            const T v = S[qx] * exp(-t_act / S[qx]);
+                            arr[qx] = ((S[qx] > t_ig) & (F[qx] > fthr)) ? v : T(0);
+                        }
+                    }
+#pragma unroll
+                    for (int qx = 0; qx < Q; ++qx) {
+                        const T a0 = ign * arr[qx];
+                        const T af = F[qx] * (cff - rate * arr[qx]);
 #pragma unroll
                         for (int i = 0; i < Q; ++i) {
                             acc0[(ph + i) % Q][qy] += a0 * T(tval<P>(i, qx));
@@ -537,7 +588,7 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
         } else {
 #pragma unroll
             for (int q = 0; q < Q; ++q) acc0[snew][q] = acc1[snew][q] = T(0);
-            live[snew] = false;
+            live[snew] = fuel = false;
         }
         // rows of the open-knot test functions at the ends of x (from_uniform,
         // on sums that are linear in the elements: partial ones of a tile too)
@@ -624,14 +675,14 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
 
     // one copy of the step per ring phase (not a second set for the last
     // steps): the code of a launch has to stay in the instruction cache
-    for (int k = 0; k < K; k += Q) {
-        step(Ic<0>{}, k);
-        if (k + 1 < K) step(Ic<1>{}, k + 1);
+    for (int n = 0; n < K; n += Q) {
+        step(Ic<0>{}, n);
+        if (n + 1 < K) step(Ic<1>{}, n + 1);
         if constexpr (Q > 2) {
-            if (k + 2 < K) step(Ic<2>{}, k + 2);
+            if (n + 2 < K) step(Ic<2>{}, n + 2);
         }
         if constexpr (Q > 3) {
-            if (k + 3 < K) step(Ic<3>{}, k + 3);
+            if (n + 3 < K) step(Ic<3>{}, n + 3);
         }
     }
 }

@@ -154,18 +154,30 @@ double assembly_work(const iga_plan *pl)
 }
 
 // Default tile height.  Small launches leave most of the chip idle, and a
-// launch lasts as long as one wavefront marches its tile and halo: the
-// smallest tiles are fastest (64^2 p = 2 FP64, both assemblies: 29 us at 4 rows,
-// 74 at 16).  Large launches are bound by VALU issue and want few halo rows.
-// Between, the best height of a sweep over 64^2 .. 4096^2 grows like the cube
-// root of the launch (1024^2 / 4096^2: FP32 5 / 11 rows for p <= 2, 5 / 16 for
-// p = 3; FP64 6 / 16 for p <= 2, 10 / 24 for p = 3); heights next to it cost a few
-// per cent.
+// launch lasts as long as one wavefront marches its tile and halo: the smallest
+// tiles (p + 1 rows) are fastest (a 64^2 p = 2 FP64 step: 73 us at 3 rows, 78 at
+// 4, 85 at 5).  Large launches are bound by VALU issue and want few halo rows.
+// Between, the best height of a sweep of steps over 64^2 .. 4096^2 grows like the
+// square root of the launch (best heights at 1024^2, 2048^2, 4096^2: FP32 p = 2
+// 5, 6, 11 and p = 3 5, 8, 18; FP64 p = 2 5, 7, 18 and p = 3 6, 12, 24); heights
+// next to it cost a few per cent.  Where one more row lets all workgroups be on
+// the chip at once it is taken (512^2 p = 3 FP64: 297 workgroups of 4 rows 166 us a
+// step, 234 of 5 rows 153).
 int default_assembly_rows(const iga_plan *pl, double work)
 {
-    const double f = pl->fp32 ? (pl->P == 3 ? 4.0 : 5.2) : (pl->P == 3 ? 2.6 : 4.0);
-    return std::max(4, (int)std::lround(std::cbrt(work) / f));
+    const int P = pl->P;
+    const double f = pl->fp32 ? (P == 3 ? 30 : 45) : P == 1 ? 45 : P == 2 ? 29 : 22;
+    const int rows = std::max(P + 1, (int)std::lround(std::sqrt(work) / f));
+    // resident workgroups of four wavefronts per compute unit, by registers
+    const double resident = 256.0 * (pl->fp32 ? (P == 1 ? 8 : P == 2 ? 4 : 2) : (P == 1 ? 3 : P == 2 ? 2 : 1));
+    return rows + (work / (4 * rows) > resident && work / (4 * (rows + 1)) <= resident);
 }
+
+// Tiles share halos within a workgroup except in the largest launches, where
+// the halos are a small part and wavefronts that do not wait for each other fill
+// the chip better (steps at 3000^2 / 4096^2, stacked to unstacked: FP32 p = 2 284 to
+// 294 / 489 to 485 us, FP64 p = 2 643 to 645 / 1142 to 1123).
+int default_assembly_stacking(double work) { return work < 2e5; }
 
 // workgroups of one assembly launch: four tiles of one strip each (stacked),
 // or four wavefronts on neighbouring strips of a tile row

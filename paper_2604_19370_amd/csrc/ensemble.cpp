@@ -220,10 +220,13 @@ iga_status iga_ensemble_create(const iga_plan_desc *members, int32_t n, iga_ense
         }
         e->plans.push_back(pl);
     }
-    // the assembly's tile height follows from the whole launch
+    // the assembly's tiles follow from the whole launch, and are of one kind
     double work = 0;
     for (const iga_plan *pl : e->plans) work += assembly_work(pl);
-    for (iga_plan *pl : e->plans) pl->asm_rows = default_assembly_rows(pl, work);
+    for (iga_plan *pl : e->plans) {
+        pl->asm_rows = default_assembly_rows(pl, work);
+        pl->asm_stack = 1;
+    }
     // one schedule per direction for all members, so that members of equal
     // line-solve shape share a launch
     if ((st = set_window_all(e, 0, 4, 17)) || (st = set_window_all(e, 1, 2, 17))) {

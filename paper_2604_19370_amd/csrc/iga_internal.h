@@ -240,6 +240,7 @@ iga_status launch_assemble(const iga_plan *pl, int substep, const void *T, const
 // height for a launch of `work` of them (one plan, or all of an ensemble)
 double assembly_work(const iga_plan *pl);
 int default_assembly_rows(const iga_plan *pl, double work);
+int default_assembly_stacking(double work);
 
 // kernels (sweep.hip)
 struct SweepJob {
@@ -307,7 +308,7 @@ iga_status launch_nonfinite(const iga_plan *pl, const void *T, const void *fuel,
 // list is fine-grained because the kernel time is set by the most loaded
 // compute unit: on small meshes one more row per wavefront can remove a whole
 // extra round of workgroups from some compute units.
-#define ASSEMBLY_ROW_CANDIDATES {4, 5, 6, 7, 8, 9, 10, 11, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64}
+#define ASSEMBLY_ROW_CANDIDATES {2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64}
 
 // the launches of one step of a plan on fields (T, fuel) (api.cpp)
 struct StepPhases {

@@ -49,3 +49,23 @@ def test_step_on_rectangular_elements(p, precision):
     pl, od = plan_and_oracle(sc, precision)
     per_step_parity(pl, od, sc, 2, precision)
     pl.close()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_fuel_rows_are_followed_through_cold_and_ambient_rows(p, precision):
+    """The fuel is read only where elements are hot, and followed row by row
+    while they are: tiles that march through hot bands of one to three rows,
+    rows that are warm without being hot, and ambient ones between them (where
+    nothing is read), from cold and hot first rows."""
+    for first in (0, 5):
+        sc = scenario(44, 70, p, "strang", 11)
+        T = np.full_like(sc.T0, 300.0)
+        for lo, hi, value in ((first, first + 3, 900.0), (12, 13, 800.0), (13, 15, 310.0), (22, 24, 700.0),
+                              (24 + p, 25 + p, 850.0), (38, 40, 305.0), (43, 44, 900.0)):
+            T[lo:hi] = value
+        sc = dataclasses.replace(sc, T0=T)
+        pl, od = plan_and_oracle(sc, precision)
+        pl.set_assembly_rows(64)
+        per_step_parity(pl, od, sc, 1, precision)
+        pl.close()
