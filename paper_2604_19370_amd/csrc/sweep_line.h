@@ -139,7 +139,13 @@ __device__ __forceinline__ void line_edges(double *tab, const double *rows, int 
 {
     using E = LineEdge<T, P>;
     constexpr int HL = E::S::HL;
-    for (int i = threadIdx.x; i < E::N; i += blockDim.x) {
+    // all loads, then all stores: one latency, not one per round (a 64^2 FP64
+    // x sweep 7.2 -> 6.9 us)
+    constexpr int NT = E::S::NW * 64, IT = (E::N + NT - 1) / NT;
+    double v[IT];
+#pragma unroll
+    for (int n = 0; n < IT; ++n) {
+        const int i = min(n * NT + (int)threadIdx.x, E::N - 1);
         int r, c;
         if (i < E::U) {
             r = R0 - HL + i / P;
@@ -152,7 +158,12 @@ __device__ __forceinline__ void line_edges(double *tab, const double *rows, int 
             c = 2 * P + 1 + (i - E::V) % P;
         }
         const int k = r < 0 || r >= N ? nrows - 1 : min(r, K0) + max(0, r - NK + 1);
-        tab[i] = rows[k * LineRow<P>::value + c];
+        v[n] = rows[k * LineRow<P>::value + c];
+    }
+#pragma unroll
+    for (int n = 0; n < IT; ++n) {
+        const int i = n * NT + (int)threadIdx.x;
+        if (i < E::N) tab[i] = v[n];
     }
 }
 
@@ -334,6 +345,19 @@ __device__ __forceinline__ void line_tile(const LineParams<P> &prm, const LineJo
                                      (size_t)(line0 + k * LPI) * ld * sizeof(T) + vo);
     };
     auto ok = [&](int k) { return (!EDGE || col < N) && line0 + k * LPI + sl < prm.nlines; };
+    // the base field's values in the order of the stores: by edge tiles (all there
+    // is on small meshes, where a launch is one chain of latencies) requested with
+    // the tile, by interior ones before the back substitution (with the tile they
+    // cost more than they hid: 4096^2 FP32 68 -> 75 us for the T and fuel jobs).
+    // y-lines of 64^2 FP64 10.3 -> 8.7 us, 1024^2 FP64 12.9 -> 11.2
+    T bs[MM];
+    auto request = [&](bool want) {
+        if constexpr (DIRY && !BAND) {
+#pragma unroll
+            for (int k = 0; k < MM; ++k) bs[k] = want && ok(k) ? *at_store(job.base, k) : T(0);
+        }
+    };
+    if (EDGE) request(job.base);
     __syncthreads();
     // tile row wave*MM + i (line row r0 - HL - PD + i) of this lane's line
     const int tb = DIRY ? lane * S::LD + wave * MM : wave * MM * 64 + lane;
@@ -426,14 +450,7 @@ __device__ __forceinline__ void line_tile(const LineParams<P> &prm, const LineJo
                 }
         }
     } else {
-        // the base field's values in the order of the stores, requested before
-        // the back substitution (requested before the eliminations they cost
-        // more than they hid: 4096^2 FP32 68 -> 75 us for the T and fuel jobs)
-        T bs[MM];
-        if constexpr (!BAND) {
-#pragma unroll
-            for (int k = 0; k < MM; ++k) bs[k] = job.base && !skip && ok(k) ? *at_store(job.base, k) : T(0);
-        }
+        if (!EDGE) request(job.base && !skip);
         if (!BAND) a.finish(meet);
         __syncthreads();   // every wavefront has read its rows of the tile
         if (skip) return;
