@@ -308,7 +308,11 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
         cb[1] = lane_ahead<1>(c0, c1, lane);
         if constexpr (Q > 2) cb[2] = lane_ahead<2>(c0, c1, lane);
         if constexpr (Q > 3) cb[3] = lane_ahead<3>(c0, c1, lane);
-        if (yedge) to_uniform<T, P>(cb, ey, a.nel_y);
+        if (yedge) {
+            int e = ey;   // (its comparisons are made here, not kept as masks)
+            asm volatile("" : "+v"(e));
+            to_uniform<T, P>(cb, e, a.nel_y);
+        }
     };
     // y half of the sum factorisation of one fetched row, the largest
     // coefficient of the row within the lane's element, and whether all of
@@ -427,6 +431,32 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
     if constexpr (held)
         asm volatile("" : "+v"(kheld.rad), "+v"(kheld.cs), "+v"(kheld.frc), "+v"(kheld.nldx), "+v"(kheld.nldy),
                           "+v"(kheld.dx), "+v"(kheld.dy), "+v"(kheld.bcay), "+v"(kheld.cy));
+    // The test functions at the points: immediates, except in double, where
+    // forming one in scalar registers takes two instructions of its own each
+    // time.  p = 2 has vector registers for one of each mirrored pair
+    // (FP64 steps: 4096^2 1107 -> 1067 us, 1024^2 128.6 -> 126.2).
+    constexpr bool held_tests = held && P == 2;
+    constexpr int NH = (Q * Q + 1) / 2;
+    T tvh[NH], tdh[NH];
+    if constexpr (held_tests) {
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+            tvh[i] = T(tval<P>(i / Q, i % Q));
+            tdh[i] = T(tder<P>(i / Q, i % Q));
+            asm volatile("" : "+v"(tvh[i]));
+            if (tder<P>(i / Q, i % Q) != 0.0) asm volatile("" : "+v"(tdh[i]));
+        }
+    }
+    auto testv = [&](int i, int q) -> T {
+        const int k = i * Q + q;
+        if constexpr (held_tests) return k < NH ? tvh[k] : tvh[Q * Q - 1 - k];
+        return T(tval<P>(i, q));
+    };
+    auto testd = [&](int i, int q) -> T {
+        const int k = i * Q + q;
+        if constexpr (held_tests) return k < NH ? tdh[k] : -tdh[Q * Q - 1 - k];
+        return T(tder<P>(i, q));
+    };
     auto step = [&](auto phase, int n) {
         constexpr int ph = decltype(phase)::value;
         constexpr int snew = (ph + P) % Q;   // slot of the new coefficient row / dof row ex+P
@@ -499,15 +529,15 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
 #pragma unroll
                     for (int i = 0; i < Q; ++i) {
                         const int si = (ph + i) % Q;
-                        const double v = tval<P>(i, qx), d = tder<P>(i, qx);
+                        const double d = tder<P>(i, qx);
                         if (i == P && qx == 0) {
-                            acc0[si][qy] = a0 * T(v);
-                            acc1[si][qy] = ay * T(v);
+                            acc0[si][qy] = a0 * testv(i, qx);
+                            acc1[si][qy] = ay * testv(i, qx);
                         } else {
-                            acc0[si][qy] += a0 * T(v);
-                            acc1[si][qy] += ay * T(v);
+                            acc0[si][qy] += a0 * testv(i, qx);
+                            acc1[si][qy] += ay * testv(i, qx);
                         }
-                        if (d != 0.0) acc0[si][qy] += ax * T(d);
+                        if (d != 0.0) acc0[si][qy] += ax * testd(i, qx);
                     }
                 }
             }
@@ -628,7 +658,11 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
             // evaluated element reached stores zero (what the contraction of
             // its zero accumulators gives, +0, without evaluating it).
             auto finish = [&](T(&pb)[Q]) {
-                if (yedge) from_uniform<T, P>(pb, ey, a.nel_y);
+                if (yedge) {
+                    int e = ey;
+                    asm volatile("" : "+v"(e));
+                    from_uniform<T, P>(pb, e, a.nel_y);
+                }
                 T r = pb[0] + lane_behind<1>(pb[1]);
                 if constexpr (Q > 2) r += lane_behind<2>(pb[2]);
                 if constexpr (Q > 3) r += lane_behind<3>(pb[3]);
@@ -642,8 +676,8 @@ __device__ __forceinline__ void assemble_body(const AsmParams<T> &a, CT<AsmParam
                     T s = T(0);
 #pragma unroll
                     for (int q = 0; q < Q; ++q) {
-                        s += acc0[ph][q] * T(tval<P>(b, q));
-                        if (tder<P>(b, q) != 0.0) s += acc1[ph][q] * T(tder<P>(b, q));
+                        s += acc0[ph][q] * testv(b, q);
+                        if (tder<P>(b, q) != 0.0) s += acc1[ph][q] * testd(b, q);
                     }
                     pb[b] = eyok ? s : T(0);
                 }
