@@ -63,10 +63,12 @@ typedef enum {
 typedef enum { IGA_PR = 0, IGA_STRANG_CN = 1, IGA_EXPLICIT = 2 } iga_scheme;
 
 /* IGA_FP64: every kernel in double.
- * IGA_FP32_REFINE: state, right-hand sides and line solves in float with float
- * accumulation; the 1D LU factorisations are computed in double, and each 1D
- * solve is followed by one step of iterative refinement whose residual
- * b - A x0 is formed in double with the double operator. */
+ * IGA_FP32_REFINE: state and right-hand sides in float with float
+ * accumulation; the 1D LU factorisations are computed in double.  The steps'
+ * line-per-lane solves (below) run in double and round their result once; the
+ * windowed, column and exact solves run in float, each followed by one step of
+ * iterative refinement whose residual b - A x0 is formed in double with the
+ * double operator. */
 typedef enum { IGA_FP64 = 0, IGA_FP32_REFINE = 1 } iga_precision;
 
 typedef enum { IGA_WIND_CONST = 0, IGA_WIND_SINCOS = 1 } iga_wind_kind;
@@ -112,10 +114,10 @@ typedef struct iga_plan iga_plan;   /* opaque; owned by the library */
  * leaves unspecified.  Never fails. */
 void iga_default_coeffs(iga_coeffs *out);
 
-/* Build a plan: knots, Gauss rules, basis tables at the quadrature points, the
+/* Build a plan: knots, Gauss rules, wind samples at the quadrature points, the
  * 1D matrices M, K, G (Section 3.1) and the directional operators of the
  * scheme, uploaded to the current HIP device.  Allocates device memory (tables
- * and scratch of about 2 fields).  *out is NULL on failure.
+ * and scratch of 4 fields).  *out is NULL on failure.
  * Errors: IGA_EINVAL (NULL pointers, p not in {1,2,3}, nel < 2p+1, lengths or dt
  * not > 0, unknown enum), IGA_ENOMEM, IGA_EDEVICE. */
 iga_status iga_plan_create(const iga_plan_desc *desc, iga_plan **out);
@@ -129,9 +131,16 @@ iga_status iga_plan_dims(const iga_plan *plan, int64_t *nx, int64_t *ny, int64_t
 
 /* Factor every banded 1D operator of the plan (eq. matrixPR / matrixCN, the
  * banded structure of Section 4) with a banded LU without pivoting, in double,
- * on the device; also precomputes the chunk-transfer tables the line solves
- * use, and the float copies for IGA_FP32_REFINE plans.  Must be called once
- * before any solve; enqueued on `stream`. */
+ * on the device; also prepares the tables of the line solves.  Must be called
+ * once before any solve; enqueued on `stream`.
+ *
+ * The sweeps of the steps then solve one line per lane: 64 lines and a few
+ * chunks of 16 rows per workgroup, each chunk eliminated in double from both
+ * sides, from a zero state so many rows outside it that the restart changes
+ * nothing above rounding (as for windowed solves, below).  Where an operator
+ * decays too slowly for the rows compiled in, and from the next call on that
+ * sets a schedule of the direction, the steps use that direction's windowed,
+ * column or exact schedule; iga_line_solve, which works in place, always does. */
 iga_status iga_factor_1d(iga_plan *plan, void *stream);
 
 /* Quadrature right-hand side of one substep (weak forms eq. varPR_wildfire
@@ -223,7 +232,7 @@ iga_status iga_run(iga_plan *plan, void *T, void *fuel, int64_t nsteps, void *st
  * iga_step, with the right-hand-side scratch taken from a fixed device array
  * of IGA_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on
  * until the process ends, instead of the plan's own buffers.  Calls no
- * allocating routine.  The plan needs 2 fields (4 under column-wave x
+ * allocating routine.  The plan is accepted up to 2 fields (4 under column-wave x
  * sweeps) of ndof * element size bytes, each rounded up to 256 bytes; a plan
  * that needs more returns IGA_EINVAL (so at most about 8.3M dofs for FP32
  * plans, 4.1M for FP64).  The first call on a device looks the array's
@@ -252,8 +261,8 @@ iga_status iga_plan_schedule(const iga_plan *plan, int32_t dir, int32_t *lines,
 iga_status iga_plan_set_schedule(iga_plan *plan, int32_t dir, int32_t lines,
                                  int32_t waves_per_line);
 
-/* Windowed line solves of direction dir (the default after iga_factor_1d
- * wherever the operators allow them).  Each lane restarts forward and backward
+/* Windowed line solves of direction dir (what iga_line_solve uses after
+ * iga_factor_1d wherever the operators allow them; set here, the steps too).  Each lane restarts forward and backward
  * substitution from a zero state `warmup` rows outside its chunk of
  * rows_per_lane rows; the plan chooses warmup from the factors so that the
  * restart changes the result by less than 2^-55 relative to the state (FP64
@@ -291,7 +300,8 @@ int32_t iga_plan_window_buffers(const iga_plan *plan, int32_t dir);
  * follow iga_factor_1d; on failure the previous schedule is kept. */
 iga_status iga_plan_set_column_schedule(iga_plan *plan, int32_t rows_per_chunk);
 
-/* Solver of direction dir: *windowed = 2 for column waves, 1 for windowed
+/* Solver of direction dir as set (the line-per-lane sweeps of the steps lie over
+ * it): *windowed = 2 for column waves, 1 for windowed
  * solves, 0 for the exact chunk scan of iga_plan_set_schedule; *warmup = the
  * windowed warm-up rows (0 if windowed solves are not possible or before
  * factorisation).  Either pointer may be NULL. */
@@ -316,7 +326,8 @@ int32_t iga_plan_assembly_stacking(const iga_plan *plan);
  * substep for every tile height (stacked and unstacked) and the line solves
  * of each direction for every windowed and exact schedule that fits, on the
  * plan's scratch buffers (T and fuel are only read), and keeps the fastest
- * of each (column waves included for the x-lines of FP32 plans).  The eight
+ * of each (line-per-lane solves included, and column waves for the x-lines of
+ * FP32 plans).  The eight
  * fastest assembly tilings, then the eight fastest line-solve schedules of
  * each direction, then the tilings once more beside the chosen line solves,
  * are timed again as a captured graph of reps steps (as
@@ -333,9 +344,10 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
  * method of Sections 3-4 on its own mesh.  Members may differ in grid size,
  * lengths, dt, scheme, wind, coefficients and fields, but share the degree p
  * and the precision.  Every phase of a step (the two assemblies, the four
- * line sweeps) runs as one launch over all members per line-solve schedule
- * group (members with equal rows per lane, lines per workgroup and wavefronts
- * per line), so the per-step launch count does not grow with the member
+ * line sweeps, and the Strang middle substep where it is a sweep of its own) runs
+ * as one launch over all members per line-solve schedule group (members whose
+ * steps solve one line per lane, or with equal rows per lane, lines per
+ * workgroup and wavefronts per line), so the per-step launch count does not grow with the member
  * count.  Explicit-scheme members take part in the first assembly and the
  * first two sweeps only.  Each member's result is, up to rounding, the one its own plan
  * would compute with the same line-solve schedule (the batched kernels are
@@ -354,7 +366,8 @@ iga_status iga_ensemble_size(const iga_ensemble *ens, int32_t *n);
 
 /* Kernel launches per step: 1 assembly + 1 sweep per schedule group and
  * direction, and the same again over the members that have a second phase
- * (every scheme but the explicit one). */
+ * (every scheme but the explicit one); under line-per-lane y sweeps one more for
+ * the middle substep of the Strang members. */
 iga_status iga_ensemble_launches(const iga_ensemble *ens, int32_t *per_step);
 
 /* One step of every member, in place: T[m], fuel[m] are member m's fields
@@ -381,8 +394,8 @@ iga_status iga_ensemble_set_schedule(iga_ensemble *ens, int32_t dir, int32_t lin
  * member needing 1/f of them takes f times the lines per workgroup where
  * that fits, so that its workgroups have the same size and it shares their
  * launch (members of one launch share rows per lane and workgroup size).
- * The default after iga_ensemble_create is (4, 17) along x and (2, 17) along
- * y. */
+ * After iga_ensemble_create it is (4, 17) along x and (2, 17) along y, for the
+ * members whose steps cannot solve one line per lane. */
 iga_status iga_ensemble_set_window_schedule(iga_ensemble *ens, int32_t dir, int32_t lines,
                                             int32_t rows_per_lane);
 /* As iga_plan_set_assembly_rows, on every member (rows >= p + 1). */
@@ -391,8 +404,8 @@ iga_status iga_ensemble_set_assembly_rows(iga_ensemble *ens, int32_t rows);
 iga_status iga_ensemble_set_assembly_stacking(iga_ensemble *ens, int32_t stacked);
 
 /* Autotuner of the batched launches: tile height and stacking of the
- * assembly, and the line-solve schedule of each direction (windowed rows per
- * lane or exact waves per line, lines per workgroup) timed on both of the
+ * assembly, and the line-solve schedule of each direction (line per lane,
+ * windowed rows per lane or exact waves per line, lines per workgroup) timed on both of the
  * step's launches of that direction with the step's own jobs; all timed with
  * HIP events on `stream` on the members' scratch buffers (the fields are
  * only read).  Synchronises. */

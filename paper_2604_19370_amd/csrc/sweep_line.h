@@ -43,9 +43,9 @@
 // Bound by latency on small meshes (1024^2: 289 workgroups, about one per
 // compute unit: fill, eliminate, write), by memory on large ones.  Against the
 // windowed and chunk-scan solves in the steps: 4096^2 FP32, x 50 -> 36 us (one
-// field; 3.7 TB/s of the 4.7 a copy reaches), y 104-113 -> 68 us (T with the
-// fuel's zero check); double, x 270 -> 77, y 196 -> 120 (T alone); cubic 1500^2
-// double x 119 -> 20, y 111 -> 22; 64^2 double x 11.8 -> 7.3, y 11.2 -> 10.3.
+// field; 3.7 TB/s of the 4.7 a copy reaches), y 104-113 -> 65 us (T with the
+// fuel's zero check); double, x 270 -> 77, y 196 -> 115 (T alone); cubic 1500^2
+// double x 119 -> 20, y 111 -> 21; 64^2 double x 11.8 -> 6.9, y 11.2 -> 8.4.
 #pragma once
 #include "sweep_kernels.h"
 
