@@ -307,6 +307,11 @@ iga_status iga_plan_set_column_schedule(iga_plan *plan, int32_t rows_per_chunk);
  * factorisation).  Either pointer may be NULL. */
 iga_status iga_plan_solver(const iga_plan *plan, int32_t dir, int32_t *windowed, int32_t *warmup);
 
+/* Whether the steps solve direction dir one line per lane (see iga_factor_1d):
+ * 1 if so, 0 if they run the solver that iga_plan_solver names, -1 for a NULL
+ * plan or a bad dir. */
+int32_t iga_plan_line_per_lane(const iga_plan *plan, int32_t dir);
+
 /* Assembly schedule: dof rows per wavefront tile, at least p + 1
  * (IGA_EINVAL below).  A workgroup takes four consecutive tiles of a strip.
  * Stacked (1): only its first tile, p rows shorter than the others,

@@ -481,6 +481,12 @@ iga_status iga_plan_solver(const iga_plan *plan, int32_t dir, int32_t *windowed,
     return IGA_OK;
 }
 
+int32_t iga_plan_line_per_lane(const iga_plan *plan, int32_t dir)
+{
+    if (!plan || (dir != 0 && dir != 1)) return -1;
+    return plan->sched[dir].line ? 1 : 0;
+}
+
 iga_status iga_plan_set_assembly_rows(iga_plan *plan, int32_t rows)
 {
     if (!plan) return fail(IGA_EINVAL, "plan is NULL");

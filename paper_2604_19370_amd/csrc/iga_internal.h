@@ -83,7 +83,7 @@ struct Schedule {
     int col = 0;   // 1 (x-lines, FP32): column waves, mm rows per chunk (sweep_col.h)
     int compact = 0;   // windowed: one line buffer per line (see WSweepParams)
     // 1: the steps use the line-per-lane solves (sweep_line.h) in place of the
-    // above; iga_line_solve, in place, does not
+    // above (iga_plan_line_per_lane); iga_line_solve, in place, does not
     int line = 0;
 };
 

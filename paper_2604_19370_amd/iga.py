@@ -34,6 +34,7 @@ EXPORTED = ("iga_default_coeffs", "iga_plan_create", "iga_plan_destroy", "iga_pl
             "iga_plan_set_assembly_stacking", "iga_plan_assembly_stacking",
             "iga_ensemble_set_assembly_stacking", "iga_step_noalloc", "iga_sample_points",
             "iga_count_ambiguous", "iga_plan_set_window_buffers", "iga_plan_window_buffers",
+            "iga_plan_line_per_lane",
             "iga_last_error")
 
 _COEFF_NAMES = ("c_adv", "c_diff", "c_react", "c_nld", "c_ign", "t_ig", "fuel_thr", "t_act",
@@ -124,11 +125,13 @@ def lib() -> ctypes.CDLL:
         L.iga_plan_set_window_buffers.argtypes = [vp, i32, i32]
         L.iga_plan_window_buffers.argtypes = [vp, i32]
         L.iga_plan_window_buffers.restype = i32
+        L.iga_plan_line_per_lane.argtypes = [vp, i32]
+        L.iga_plan_line_per_lane.restype = i32
         L.iga_last_error.argtypes = []
         L.iga_last_error.restype = ctypes.c_char_p
         for name in EXPORTED[1:-1]:
             if name not in ("iga_plan_assembly_rows", "iga_plan_assembly_stacking",
-                            "iga_plan_window_buffers"):
+                            "iga_plan_window_buffers", "iga_plan_line_per_lane"):
                 getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -361,6 +364,10 @@ class Plan:
         _check(lib().iga_plan_solver(self._h, int(dir), ctypes.byref(w), ctypes.byref(h)),
                "iga_plan_solver")
         return dict(windowed=bool(w.value), warmup=h.value, column=w.value == 2)
+
+    def line_per_lane(self, dir) -> bool:
+        """Whether the steps solve `dir` one line per lane (else as solver(dir) says)."""
+        return int(lib().iga_plan_line_per_lane(self._h, int(dir))) == 1
 
 
 class Ensemble:

@@ -1,0 +1,58 @@
+"""Which solver the steps run: line-per-lane solves on every mesh whose lines
+have at least 4p + 1 dofs and whose operators decay within the compiled halo, the
+direction's own schedule elsewhere and after a call that sets one; and the
+steps of the shortest lines of either kind, against the oracle."""
+import pytest
+
+from paper_2604_19370_amd import inputs
+from test_gpu_line import SHAPES
+from test_gpu_parity import per_step_parity, plan_and_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def routes(pl):
+    return pl.line_per_lane(0), pl.line_per_lane(1)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_shortest_lines(p, precision):
+    """nel = 3p + 1 is the shortest that steps solve one line per lane."""
+    short, first, long = 3 * p, 3 * p + 1, 97
+    for ex, ey in [(2 * p + 1, 2 * p + 1), (short, long), (long, short), (first, first + 1),
+                   (first + 1, long), (long, first)]:
+        for scheme in ("strang", "pr"):
+            print(f"{scheme} {ex}x{ey} p{p} {precision}", flush=True)
+            sc = inputs.small_case(ex + 3 * ey + p, ex, ey, p, scheme)
+            pl, od = plan_and_oracle(sc, precision)
+            assert routes(pl) == (ex >= first, ey >= first)
+            per_step_parity(pl, od, sc, 1, precision)
+            pl.close()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_tile_edge_shapes_run_line_per_lane(p, precision):
+    """The shapes of the tile-edge test, but its smallest mesh."""
+    for nx, ny in SHAPES[1:]:
+        sc = inputs.small_case(nx + ny + p, nx - p, ny - p, p, "strang")
+        pl, _ = plan_and_oracle(sc, precision)
+        assert routes(pl) == (True, True), (nx, ny)
+        pl.close()
+
+
+def test_slow_decay_and_set_schedules():
+    sc = inputs.small_case(9, 200, 36, 2, "pr", dt=400.0)
+    pl, _ = plan_and_oracle(sc, "fp64", coeffs=dict(c_nld=0.0, c_ign=0.0, c_rad=0.0, c_forcing=0.0))
+    assert not pl.line_per_lane(0)
+    pl.close()
+    sc = inputs.small_case(10, 90, 70, 2, "strang")
+    pl, _ = plan_and_oracle(sc, "fp32")
+    for set_x in (lambda: pl.set_schedule(0, 2, 1), lambda: pl.set_window_schedule(0, 2, 17),
+                  lambda: pl.set_column_schedule(16)):
+        pl.factor()
+        assert routes(pl) == (True, True)
+        set_x()
+        assert routes(pl) == (False, True)
+    pl.close()
