@@ -132,14 +132,17 @@ static bool canonical(const LineHostOp &h, std::vector<double> &k)
 
 // Line-per-lane solves of direction dir.  Used by the steps (out of place);
 // iga_line_solve keeps the direction's windowed or exact schedule.
-// IGA_EUNSUPPORTED if an operator decays too slowly for the compiled halo or
-// has no short edges.
+// IGA_EUNSUPPORTED if an operator decays too slowly for the compiled halo, has
+// long edges, or the lines are shorter than 4p + 1.
 iga_status choose_line_schedule(iga_plan *pl, int dir)
 {
     const int N = dir ? pl->Ny : pl->Nx, P = pl->P, RS = 2 * P + 2, LROW = line_row_size(P);
     const LineShape sh = line_shape(pl);
     const double tol = std::ldexp(1.0, pl->fp32 ? -30 : -55);
     const int ntiles = (N + sh.own - 1) / sh.own;
+    // the kernel looks D's rows up as the first 2P, the interior one and the last
+    // 2P (LineBand), which are 4P + 1 different rows only from here on
+    if (N < 4 * P + 1) return fail(IGA_EUNSUPPORTED, "lines too short for the line-per-lane solves");
     LineHostOp h[NOPS];
     int K0 = 0, NK = N;   // rows [K0, NK) are canonical in both factorisations of every operator
     std::vector<double> consts[NOPS];
@@ -162,20 +165,17 @@ iga_status choose_line_schedule(iga_plan *pl, int dir)
         }
         OpHost t;
         interior_range(lv, N, RS, 1e-15, t.K0, t.NK);
-        if (t.NK <= t.K0) t.K0 = t.NK = N;
         t.rows = compress_rows(lv, N, RS, t.K0, t.NK);
         t.nrows = (int)(t.rows.size() / RS);
         if (compute_warmup(t, N, P, tol, sh.HL) <= 0 || !canonical(q, consts[op]))
             return fail(IGA_EUNSUPPORTED, "the operators decay too slowly for the line-per-lane halo");
     }
-    if (NK <= K0) K0 = NK = N;   // no interior: every row is stored
+    // (the middle row is in every interior range: K0 <= N/2 < NK)
     const BandHost &bd = pl->band_host[dir ? BAND_BY : BAND_BX];
     const int nrows = K0 + 1 + (N - NK) + 1;   // edge rows, the canonical one, zeros
+    if (nrows > 1024) return fail(IGA_EUNSUPPORTED, "the operators' edges are too long");
     // D's own rows are the first and last 2P
-    if (nrows > 1024 || (K0 < N && (K0 < 2 * P || N - NK < 2 * P)))
-        return fail(IGA_EUNSUPPORTED, "no uniform interior");
-    if (dir && bd.K0 < N && (bd.K0 > 2 * P || bd.NK < N - 2 * P))
-        return fail(IGA_EUNSUPPORTED, "no uniform interior");
+    if (dir && (bd.K0 > 2 * P || bd.NK < N - 2 * P)) return fail(IGA_EUNSUPPORTED, "no uniform interior");
     // tiles whose rows are all canonical and inside the line
     auto interior = [&](int t) {
         const int a = t * sh.own - sh.HL - P, e = (t + 1) * sh.own + sh.HL + P;
@@ -203,7 +203,7 @@ iga_status choose_line_schedule(iga_plan *pl, int dir)
             std::copy(f, f + 2 * P + 1, &t[(size_t)i * LROW]);
             std::copy(b, b + P, &t[(size_t)i * LROW + 2 * P + 1]);
         };
-        for (int r = 0; r < std::min(K0 + 1, N); ++r) put(r, r);
+        for (int r = 0; r <= K0; ++r) put(r, r);
         for (int r = NK; r < N; ++r) put(K0 + 1 + r - NK, r);
         add(first, t);
         t.assign((size_t)std::max(1, nedge) * sh.NW * 2 * P * P, 0.0);
