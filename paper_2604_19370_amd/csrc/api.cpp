@@ -547,8 +547,8 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
     // line solves: lines per workgroup, timed on the step's own jobs
     auto apply = [&](int dir, const Schedule &sc) {
         iga_status e;
-        if (sc.col) return choose_column_schedule(plan, sc.mm);
-        if (sc.win) e = choose_window_schedule(plan, dir, sc.lines, sc.mm);
+        if (sc.col) e = choose_column_schedule(plan, sc.mm);
+        else if (sc.win) e = choose_window_schedule(plan, dir, sc.lines, sc.mm);
         else e = choose_schedule(plan, dir, sc.lines, sc.wpl);
         return e || !sc.line ? e : choose_line_schedule(plan, dir);
     };

@@ -55,7 +55,8 @@ extern "C" iga_status iga_step_noalloc(iga_plan *plan, void *T, void *fuel, void
     if (!plan->factored) return fail(IGA_ESTATE, "iga_factor_1d has not been called");
     // fields rounded up to 256 bytes so each starts aligned
     const size_t field = (plan->ndof * plan->wsize + 255) & ~size_t(255);
-    const int nfields = plan->sched[0].col ? 4 : 2;
+    // (column waves beneath line-per-lane x sweeps are not the step's)
+    const int nfields = plan->sched[0].col && !plan->sched[0].line ? 4 : 2;
     if (nfields * field > SCRATCH_BYTES)
         return fail(IGA_EINVAL, "iga_step_noalloc: the plan needs " +
                                     std::to_string(nfields * field) + " bytes of scratch, above " +
