@@ -329,17 +329,19 @@ int32_t iga_plan_assembly_stacking(const iga_plan *plan);
 
 /* Autotuner: times, with HIP events on `stream`, the assembly of the first
  * substep for every tile height (stacked and unstacked) and the line solves
- * of each direction for every windowed and exact schedule that fits, on the
- * plan's scratch buffers (T and fuel are only read), and keeps the fastest
- * of each (line-per-lane solves included, and column waves for the x-lines of
- * FP32 plans).  The eight
+ * of each direction for every windowed and exact schedule that fits (and
+ * column waves for the x-lines of FP32 plans), on the plan's scratch buffers
+ * (T and fuel are only read).  The eight
  * fastest assembly tilings, then the eight fastest line-solve schedules of
  * each direction, then the tilings once more beside the chosen line solves,
  * are timed again as a captured graph of reps steps (as
  * iga_run replays them; the fastest of three replays counts), on device
  * copies of T and fuel that the call allocates and frees, and the fastest
- * step wins.  Synchronises `stream`; must follow iga_factor_1d.  reps >= 1
- * launches (or steps) per candidate. */
+ * step wins.  The fastest schedule is kept for iga_line_solve; the steps run it
+ * too, or line-per-lane solves where a step with these is faster.  (Where these
+ * lie over column waves, iga_line_solve(0, 2) runs the fastest windowed or exact
+ * schedule instead of being refused.)  Synchronises `stream`; must follow
+ * iga_factor_1d.  reps >= 1 launches (or steps) per candidate. */
 iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t reps,
                         void *stream);
 

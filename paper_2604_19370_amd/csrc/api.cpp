@@ -301,8 +301,12 @@ iga_status iga_line_solve(const iga_plan *plan, int32_t dir, int32_t which, void
     if (which == 1) j.op0 = M;
     if (plan->sched[dir].col) {
         // column waves solve out of place: through the plan's scratch field
-        if (which == 2)
-            return fail(IGA_EUNSUPPORTED, "x <- A^{-1} B x needs a windowed or exact x schedule");
+        if (which == 2) {
+            if (!plan->x_cn.lines)
+                return fail(IGA_EUNSUPPORTED, "x <- A^{-1} B x needs a windowed or exact x schedule");
+            j = SweepJob{x, x, -1, B, A, nullptr, 1};
+            return launch_sweep(plan, dir, &j, 1, s, &plan->x_cn);
+        }
         j.dst = plan->scratch_r2.ptr;
         if ((st = launch_sweep(plan, dir, &j, 1, s))) return st;
         IGA_HIP(hipMemcpyAsync(x, plan->scratch_r2.ptr, plan->ndof * plan->wsize,
@@ -544,15 +548,35 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
         plan->asm_stack = best_stack;
         if ((st = launch_assemble(plan, 0, T, fuel, R, RF, true, s))) return st;
     }
-    // line solves: lines per workgroup, timed on the step's own jobs
+    // line solves: lines per workgroup, timed on the step's own jobs.  The
+    // column, windowed and exact candidates compete for what iga_line_solve runs
+    // (and the steps, where line-per-lane solves do not win or are not possible);
+    // line-per-lane solves lie over the fastest of them.
     auto apply = [&](int dir, const Schedule &sc) {
-        iga_status e;
-        if (sc.col) e = choose_column_schedule(plan, sc.mm);
-        else if (sc.win) e = choose_window_schedule(plan, dir, sc.lines, sc.mm);
-        else e = choose_schedule(plan, dir, sc.lines, sc.wpl);
-        return e || !sc.line ? e : choose_line_schedule(plan, dir);
+        if (sc.col) return choose_column_schedule(plan, sc.mm);
+        if (sc.win) return choose_window_schedule(plan, dir, sc.lines, sc.mm);
+        return choose_schedule(plan, dir, sc.lines, sc.wpl);
     };
-    std::vector<std::pair<float, Schedule>> timed[2];   // every candidate, launched alone
+    using Timed = std::pair<float, Schedule>;
+    auto faster = [](const Timed &a, const Timed &b) { return a.first < b.first; };
+    std::vector<Timed> timed[2];     // every candidate beneath, launched alone
+    bool line[2] = {false, false};   // line-per-lane solves are possible
+    // Candidate `below` of direction dir with line-per-lane solves over it.
+    // Column waves do not solve A^{-1} B: the fastest candidate that does is kept
+    // beside them.
+    auto apply_line = [&](int dir, const Schedule &below) {
+        Schedule cn{0};
+        if (below.col)
+            for (const Timed &t : timed[dir])   // (sorted)
+                if (!t.second.col && apply(dir, t.second) == IGA_OK) {
+                    cn = plan->sched[dir];
+                    break;
+                }
+        iga_status e = apply(dir, below);
+        if (!e) e = choose_line_schedule(plan, dir);
+        if (!e && dir == 0) plan->x_cn = cn;
+        return e;
+    };
     for (int dir = 0; dir < 2; ++dir) {
         SweepJob jobs[2];
         int nj;
@@ -567,31 +591,32 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
             jobs[0] = SweepJob{R, out.ptr, OP_MY, -1, -1, T, 0};
             nj = 1;
         }
-        const Schedule keep = plan->sched[dir];
-        Schedule best = keep;
+        Schedule best = plan->sched[dir];
         float best_ms = 1e30f;
-        auto consider = [&] {
-            float ms;
+        auto time_sweep = [&] {
             if (dir && plan->sched[1].line && plan->d.scheme == IGA_STRANG_CN) {
                 // S1's solve and S2 are two launches
                 const SweepJob y{R, out.ptr, OP_MY, -1, -1, T, 0}, m{out.ptr, out2, -1, BAND_BY, OP_AY, nullptr, 1};
-                ms = time_launches(s, reps, [&] {
+                return time_launches(s, reps, [&] {
                     iga_status e = launch_sweep(plan, dir, &y, 1, s);
                     return e ? e : launch_sweep(plan, dir, &m, 1, s);
                 });
-            } else {
-                ms = time_launches(s, reps, [&] { return launch_sweep(plan, dir, jobs, nj, s); });
             }
+            return time_launches(s, reps, [&] { return launch_sweep(plan, dir, jobs, nj, s); });
+        };
+        auto consider = [&] {
+            const float ms = time_sweep();
             if (ms >= 0) timed[dir].emplace_back(ms, plan->sched[dir]);
             if (ms >= 0 && ms < best_ms) {
                 best_ms = ms;
                 best = plan->sched[dir];
             }
         };
-        // line-per-lane solves on top of the current schedule, column waves
-        // (x-lines, FP32), then windowed solves (where the operators decay
-        // fast enough)
-        if (choose_line_schedule(plan, dir) == IGA_OK) consider();
+        // line-per-lane solves, column waves (x-lines, FP32), then windowed
+        // solves (where the operators decay fast enough)
+        float line_ms = -1.f;
+        if (choose_line_schedule(plan, dir) == IGA_OK) line_ms = time_sweep();
+        line[dir] = line_ms >= 0;
         if (dir == 0)
             for (int mm : {16, 32})
                 if (choose_column_schedule(plan, mm) == IGA_OK) consider();
@@ -609,7 +634,8 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
                 consider();
             }
         }
-        if ((st = apply(dir, best))) return st;
+        std::stable_sort(timed[dir].begin(), timed[dir].end(), faster);
+        if ((st = line[dir] && line_ms < best_ms ? apply_line(dir, best) : apply(dir, best))) return st;
     }
     // Refinement: the fastest few assembly tilings, then the fastest few
     // line-solve candidates of each direction, again, timed
@@ -667,10 +693,8 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
         };
         refine_assembly();
         for (int dir = 0; dir < 2; ++dir) {
-            auto &c = timed[dir];
-            std::stable_sort(c.begin(), c.end(),
-                             [](const auto &a, const auto &b) { return a.first < b.first; });
-            if (c.size() < 2) continue;
+            const auto &c = timed[dir];
+            if (c.size() + line[dir] < 2) continue;
             Schedule best = plan->sched[dir];
             float best_ms = 1e30f;
             for (size_t i = 0; i < std::min(c.size(), NREFINE); ++i) {
@@ -680,6 +704,11 @@ iga_status iga_autotune(iga_plan *plan, const void *T, const void *fuel, int32_t
                     best_ms = ms;
                     best = c[i].second;
                 }
+            }
+            if (line[dir]) {
+                if ((st = apply_line(dir, best))) return st;
+                const float ms = step_ms();
+                if (ms >= 0 && ms < best_ms) continue;
             }
             if ((st = apply(dir, best))) return st;
         }

@@ -174,6 +174,9 @@ struct iga_plan {
     std::vector<double> op_band[iga::NOPS];    // host FP64 operators
     std::vector<double> cn_band[iga::NBANDS];  // explicit CN operators, B - A
     iga::Schedule sched[2];
+    // where the autotuner left column waves beneath line-per-lane x sweeps, which
+    // do not solve A^{-1} B: the schedule that does (lines 0: none)
+    iga::Schedule x_cn{0};
     int win_buffers[2] = {0, 0};   // requested windowed LDS form: 0 automatic, 1 or 2 buffers
     int asm_rows = 16;
     int asm_stack = 0;   // assembly tiles share halos within four-tile workgroups
@@ -257,8 +260,9 @@ struct SweepJob {
     // writes the zeros instead of solving
     int zero_skip = 0;
 };
+// as: schedule to use in place of the direction's (its tables have to be built)
 iga_status launch_sweep(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs,
-                        hipStream_t s);
+                        hipStream_t s, const Schedule *as = nullptr);
 // column-wave x-line solves (sweep_col.hip): out of place, single solves
 bool csweep_ok(const iga_plan *pl);
 bool csweep_rows_ok(int mm);

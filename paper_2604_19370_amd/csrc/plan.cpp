@@ -649,6 +649,7 @@ iga_status choose_schedule(iga_plan *pl, int dir, int lines, int wpl)
                                           " lines does not fit in LDS");
     }
     sc.lines = lines;
+    if (dir == 0) pl->x_cn.lines = 0;
     iga_status st;
     if (old.wpl != sc.wpl || old.mm != sc.mm || old.win || old.col)
         if ((st = build_scan_tables(pl, dir))) return st;
@@ -696,6 +697,7 @@ iga_status choose_window_schedule(iga_plan *pl, int dir, int lines, int mm)
     sc.win = 1;
     sc.col = 0;
     sc.line = 0;
+    if (dir == 0) pl->x_cn.lines = 0;
     iga_status st = build_window_tables(pl, dir);
     if (!st) st = wsweep_prepare(pl, dir);
     if (st) {
@@ -726,6 +728,7 @@ iga_status choose_column_schedule(iga_plan *pl, int mm)
     sc.win = 0;
     sc.col = 1;
     sc.line = 0;
+    pl->x_cn.lines = 0;
     return IGA_OK;
 }
 

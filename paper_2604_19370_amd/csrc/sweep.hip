@@ -76,11 +76,10 @@ static SweepBatchFn pick_batch_fn(bool fp32, int P, int mm, bool diry)
     return nullptr;
 }
 
-static iga_status build_params(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs,
-                               SweepParams &prm)
+static iga_status build_params(const iga_plan *pl, const Schedule &sc, int dir, const SweepJob *jobs,
+                               int njobs, SweepParams &prm)
 {
     if (njobs < 1 || njobs > MAXJOBS) return fail(IGA_EINVAL, "bad sweep job count");
-    const Schedule &sc = pl->sched[dir];
     std::memset(&prm, 0, sizeof prm);
     for (int j = 0; j < njobs; ++j) {
         prm.jobs[j] = jobs[j];
@@ -166,9 +165,8 @@ size_t wsweep_lds_bytes(const iga_plan *pl, int dir, int lines, int wpl, int mm,
                     : wlds(pl, g, lines, wpl, mm, 2, 1, compact);
 }
 
-static size_t wsweep_lds_jobs(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs)
+static size_t wsweep_lds_jobs(const iga_plan *pl, const Schedule &sc, int dir, const SweepJob *jobs, int njobs)
 {
-    const Schedule &sc = pl->sched[dir];
     size_t b = 0;
     for (int j = 0; j < njobs; ++j)
         b = std::max(b, wlds(pl, pl->wgeom[dir], sc.lines, sc.wpl, sc.mm,
@@ -205,11 +203,10 @@ static bool zero_skip_valid(const SweepJob &j)
            ((j.base == nullptr && j.dst == j.src) || (j.base != nullptr && j.base == j.dst));
 }
 
-static iga_status build_wparams(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs,
-                                WSweepParams &prm)
+static iga_status build_wparams(const iga_plan *pl, const Schedule &sc, int dir, const SweepJob *jobs,
+                                int njobs, WSweepParams &prm)
 {
     if (njobs < 1 || njobs > MAXJOBS) return fail(IGA_EINVAL, "bad sweep job count");
-    const Schedule &sc = pl->sched[dir];
     std::memset(&prm, 0, sizeof prm);
     for (int j = 0; j < njobs; ++j) {
         prm.jobs[j] = jobs[j];
@@ -234,10 +231,11 @@ static iga_status build_wparams(const iga_plan *pl, int dir, const SweepJob *job
 }
 
 
-iga_status launch_sweep(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs, hipStream_t s)
+iga_status launch_sweep(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs, hipStream_t s,
+                        const Schedule *as)
 {
-    const Schedule &sc = pl->sched[dir];
-    if (line_jobs_ok(pl, dir, jobs, njobs)) return launch_line(pl, dir, jobs, njobs, s);
+    const Schedule &sc = as ? *as : pl->sched[dir];
+    if (!as && line_jobs_ok(pl, dir, jobs, njobs)) return launch_line(pl, dir, jobs, njobs, s);
     if (sc.col) {
         if (dir != 0) return fail(IGA_EINVAL, "column-wave schedules are for x-lines");
         return launch_csweep(pl, jobs, njobs, s);
@@ -246,10 +244,10 @@ iga_status launch_sweep(const iga_plan *pl, int dir, const SweepJob *jobs, int n
         WSweepFn fn = pick_wfn(pl->fp32, pl->P, sc.mm, dir == 1, sc.compact != 0);
         if (!fn) return fail(IGA_EUNSUPPORTED, "windowed line-solve kernel not compiled for this schedule");
         WSweepParams prm;
-        iga_status st = build_wparams(pl, dir, jobs, njobs, prm);
+        iga_status st = build_wparams(pl, sc, dir, jobs, njobs, prm);
         if (st) return st;
         const int nblk = (prm.nlines + sc.lines - 1) / sc.lines;
-        const size_t lds = wsweep_lds_jobs(pl, dir, jobs, njobs);
+        const size_t lds = wsweep_lds_jobs(pl, sc, dir, jobs, njobs);
         if (lds > 160 * 1024) return fail(IGA_EUNSUPPORTED, "line-solve buffers do not fit in LDS");
         hipLaunchKernelGGL(fn, dim3(nblk, njobs), dim3(sc.lines * sc.wpl * 64), lds, s, prm);
         IGA_HIP(hipGetLastError());
@@ -258,7 +256,7 @@ iga_status launch_sweep(const iga_plan *pl, int dir, const SweepJob *jobs, int n
     SweepFn fn = pick_fn(pl->fp32, pl->P, sc.mm, dir == 1);
     if (!fn) return fail(IGA_EUNSUPPORTED, "line-solve kernel not compiled for this schedule");
     SweepParams prm;
-    iga_status st = build_params(pl, dir, jobs, njobs, prm);
+    iga_status st = build_params(pl, sc, dir, jobs, njobs, prm);
     if (st) return st;
     const int nblk = (prm.nlines + sc.lines - 1) / sc.lines;
     const size_t lds = sweep_lds_bytes(pl, dir, sc.lines, sc.wpl);
@@ -311,15 +309,15 @@ iga_status build_sweep_batch(const std::vector<iga_plan *> &pls, int dir,
             int nlines, njobs;
             if (key.win) {
                 WSweepParams prm;
-                iga_status st = build_wparams(pls[m], dir, jobs[m].data(), (int)jobs[m].size(), prm);
+                iga_status st = build_wparams(pls[m], sc, dir, jobs[m].data(), (int)jobs[m].size(), prm);
                 if (st) return st;
                 nlines = prm.nlines;
                 njobs = prm.njobs;
                 wprms.push_back(prm);
-                lds = std::max(lds, wsweep_lds_jobs(pls[m], dir, jobs[m].data(), (int)jobs[m].size()));
+                lds = std::max(lds, wsweep_lds_jobs(pls[m], sc, dir, jobs[m].data(), (int)jobs[m].size()));
             } else {
                 SweepParams prm;
-                iga_status st = build_params(pls[m], dir, jobs[m].data(), (int)jobs[m].size(), prm);
+                iga_status st = build_params(pls[m], sc, dir, jobs[m].data(), (int)jobs[m].size(), prm);
                 if (st) return st;
                 nlines = prm.nlines;
                 njobs = prm.njobs;

@@ -2,11 +2,13 @@
 have at least 4p + 1 dofs and whose operators decay within the compiled halo, the
 direction's own schedule elsewhere and after a call that sets one; and the
 steps of the shortest lines of either kind, against the oracle."""
+import numpy as np
 import pytest
 
+import oracle
 from paper_2604_19370_amd import inputs
 from test_gpu_line import SHAPES
-from test_gpu_parity import dev, per_step_parity, plan_and_oracle
+from test_gpu_parity import TOL32, TOL64, dev, host, per_step_parity, plan_and_oracle, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -70,4 +72,30 @@ def test_autotune_after_a_column_schedule_keeps_line_per_lane():
     assert routes(pl) == (True, True)
     per_step_parity(pl, od, sc, 1, "fp32")
     per_step_parity(pl, od, sc, 1, "fp32", step=pl.step_noalloc)
+    pl.close()
+
+
+@pytest.mark.parametrize("nx,ny,precision", [(700, 620, "fp64"), (700, 620, "fp32"), (4096, 1200, "fp32")])
+def test_autotune_chooses_the_schedule_beneath(nx, ny, precision):
+    """iga_line_solve runs the schedule beneath the steps' line-per-lane solves:
+    a poor one that was set (one line of eight wavefronts a workgroup: 24 us an
+    x solve at 700^2 for 12) does not outlast the tuner, and whatever
+    lies beneath, column waves too, every solve is served and correct."""
+    sc = inputs.small_case(nx + ny, nx, ny, 2, "strang")
+    pl, od = plan_and_oracle(sc, precision)
+    T, F = dev(sc.T0, pl.fp32), dev(sc.fuel0, pl.fp32)
+    for dir in (0, 1):
+        pl.set_schedule(dir, 1, 8)
+    pl.autotune(T, F, reps=3)
+    print(routes(pl), [dict(pl.schedule(d), **pl.solver(d)) for d in (0, 1)], flush=True)
+    assert pl.line_per_lane(0)
+    X = np.random.default_rng(nx).standard_normal((nx + 2, ny + 2))
+    for dir in (0, 1):
+        s = pl.schedule(dir)
+        assert (s["lines"], s["waves_per_line"]) != (1, 8)
+        for which in (0, 1, 2):
+            x = dev(X, pl.fp32)
+            pl.line_solve(dir, which, x)
+            assert rel(host(x), oracle.line_solve(od, dir, which, X)) < (TOL32 if pl.fp32 else TOL64), (dir, which)
+    per_step_parity(pl, od, sc, 1, precision)
     pl.close()
