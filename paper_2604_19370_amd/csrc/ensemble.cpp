@@ -386,17 +386,30 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
     // line solves: lines per workgroup x wavefronts per line (or rows per
     // lane), timed on both of the step's launches of the direction with the
     // step's own jobs (fused Crank-Nicolson solves, base states, zero skips),
-    // every state field replaced by a scratch buffer of the member: the
-    // caller's fields are not written
-    auto spare_field = [](const iga_plan *pl) { return (pl->ndof * pl->wsize + 255) & ~size_t(255); };
-    std::vector<DevBuf> spare(n);   // in the place of every member's (T, fuel)
-    for (size_t m = 0; m < n; ++m) {
-        const iga_plan *pl = ens->plans[m];
-        IGA_HIP(spare[m].alloc(2 * spare_field(pl)));
-        char *p = spare[m].as<char>();
-        IGA_HIP(hipMemcpyAsync(p, T[m], pl->ndof * pl->wsize, hipMemcpyDeviceToDevice, s));
-        IGA_HIP(hipMemcpyAsync(p + spare_field(pl), fuel[m], pl->ndof * pl->wsize, hipMemcpyDeviceToDevice, s));
-    }
+    // every state field that they write replaced by a scratch buffer of the
+    // member: the caller's fields are not written
+    auto spare_state = [](const iga_plan *pl, const void *T, const void *F, std::vector<SweepJob> jobs) {
+        void *const scratch[4] = {pl->scratch_r.ptr, pl->scratch_rf.ptr, pl->scratch_r2.ptr, pl->scratch_rf2.ptr};
+        for (SweepJob &j : jobs) {
+            if (j.dst != T && j.dst != F) continue;
+            if (j.base && j.base != j.dst) {   // from a state in scratch: over it
+                j.dst = const_cast<void *>(j.base);
+                continue;
+            }
+            void *to = const_cast<void *>(j.src);   // in place, unless a field is free
+            for (void *f : scratch) {
+                bool free = f != nullptr;
+                for (const SweepJob &k : jobs) free = free && k.src != f && k.dst != f && k.base != f;
+                if (free) {
+                    to = f;
+                    break;
+                }
+            }
+            j.dst = to;
+            if (j.base) j.base = to;
+        }
+        return jobs;
+    };
     for (int dir = 0; dir < 2; ++dir) {
         int best_l = 0, best_w = 0, best_win = 0;
         float best_ms = 1e30f;
@@ -408,15 +421,16 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
             for (size_t m = 0; m < n; ++m) {
                 iga_plan *pl = ens->plans[m];
                 StepPhases sp;
-                step_phases(pl, spare[m].ptr, spare[m].as<char>() + spare_field(pl), sp);
-                ja[m] = dir == 0 ? sp.x1 : sp.y1;
+                step_phases(pl, T[m], fuel[m], sp);
+                auto jobs = [&](const std::vector<SweepJob> &j) { return spare_state(pl, T[m], fuel[m], j); };
+                ja[m] = jobs(dir == 0 ? sp.x1 : sp.y1);
                 if (dir && !sp.m.empty()) {
                     middle.push_back(pl);
-                    jm.push_back(sp.m);
+                    jm.push_back(jobs(sp.m));
                 }
                 if (sp.two) {
                     second.push_back(pl);
-                    jb.push_back(dir == 0 ? sp.x2 : sp.y2);
+                    jb.push_back(jobs(dir == 0 ? sp.x2 : sp.y2));
                 }
             }
             std::vector<BatchLaunch> bla, blb, blm;

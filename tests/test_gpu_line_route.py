@@ -2,15 +2,20 @@
 have at least 4p + 1 dofs and whose operators decay within the compiled halo, the
 direction's own schedule elsewhere and after a call that sets one; and the
 steps of the shortest lines of either kind, against the oracle."""
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 
 import oracle
-from paper_2604_19370_amd import inputs
+from paper_2604_19370_amd import iga, inputs
+from test_gpu_ensemble import check_vs_oracle, fields, step_input
 from test_gpu_line import SHAPES
-from test_gpu_parity import TOL32, TOL64, dev, host, per_step_parity, plan_and_oracle, rel
+from test_gpu_parity import TOL32, TOL64, dev, host, per_step_parity, plan_and_oracle, rel, upload
 
 pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
 
 
 def routes(pl):
@@ -99,3 +104,58 @@ def test_autotune_chooses_the_schedule_beneath(nx, ny, precision):
             assert rel(host(x), oracle.line_solve(od, dir, which, X)) < (TOL32 if pl.fp32 else TOL64), (dir, which)
     per_step_parity(pl, od, sc, 1, precision)
     pl.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_ensemble_of_both_kinds_of_members(precision):
+    """Members whose steps solve one line per lane in both directions, in one, and
+    in none: as created and as tuned, every step matches the oracle, and the
+    tuner leaves the fields as they are."""
+    p = 2
+    scs = [inputs.small_case(50 + i, ex, ey, p, scheme) for i, (ex, ey, scheme) in enumerate(
+        [(150, 133, "strang"), (6, 90, "strang"), (90, 6, "strang"), (5, 5, "pr"), (130, 70, "explicit"),
+         (6, 120, "explicit"), (70, 64, "pr")])]
+    for sc in scs:
+        pl, _ = plan_and_oracle(sc, precision)
+        assert routes(pl) == (sc.nel_x > 3 * p, sc.nel_y > 3 * p)
+        pl.close()
+    ens = iga.Ensemble.from_scenarios(scs, precision=precision)
+    Ts, Fs = fields(ens, scs)
+    # two groups of line solves in each sweep, and the middle substep on its own
+    assert ens.launches_per_step >= 2 + 8 + 1
+    for tuned in (False, True):
+        if tuned:
+            ens.autotune(Ts, Fs, reps=2)
+            for sc, T, F in zip(scs, Ts, Fs):
+                assert torch.equal(T, dev(step_input(sc.T0, precision), ens.fp32))
+                assert torch.equal(F, dev(step_input(sc.fuel0, precision), ens.fp32))
+        for sc, T, F in zip(scs, Ts, Fs):
+            upload(T, step_input(sc.T0, precision))
+            upload(F, step_input(sc.fuel0, precision))
+        ens.step(Ts, Fs)
+        for m, sc in enumerate(scs):
+            check_vs_oracle(sc, host(Ts[m]), host(Fs[m]), step_input(sc.T0, precision),
+                            step_input(sc.fuel0, precision), precision)
+            upload(Ts[m], step_input(sc.T0, precision))
+            upload(Fs[m], step_input(sc.fuel0, precision))
+    ens.close()
+
+
+def test_ensemble_tuner_takes_no_fields():
+    """The ensemble's tuner works on the members' scratch buffers: while it runs,
+    the device's free memory does not fall by a member's field (33.6 MB).  The
+    second of two calls is watched: the first loads the kernels."""
+    scs = [inputs.small_case(60 + i, 2048, 2048, 2, scheme) for i, scheme in enumerate(("strang", "pr"))]
+    ens = iga.Ensemble.from_scenarios(scs, precision="fp64")
+    Ts, Fs = fields(ens, scs)
+    ens.autotune(Ts, Fs, reps=1)
+    torch.cuda.synchronize()
+    free = [torch.cuda.mem_get_info()[0]]
+    with ThreadPoolExecutor(1) as ex:
+        call = ex.submit(ens.autotune, Ts, Fs, 1, torch.cuda.current_stream())
+        while not call.done():
+            free.append(torch.cuda.mem_get_info()[0])
+        call.result()
+    print(f"{len(free) - 1} readings, free memory fell by {(free[0] - min(free)) / 1e6:.1f} MB", flush=True)
+    assert len(free) > 10 and free[0] - min(free) < 8 * Ts[0].numel()
+    ens.close()
