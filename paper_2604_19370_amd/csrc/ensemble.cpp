@@ -410,10 +410,14 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
         }
         return jobs;
     };
+    struct Choice {
+        int lines = 0, w = 0, win = 0;   // w: rows per lane (win), wavefronts per line
+        bool line = false;               // line-per-lane solves over it
+    };
     for (int dir = 0; dir < 2; ++dir) {
-        int best_l = 0, best_w = 0, best_win = 0;
+        Choice best;
         float best_ms = 1e30f;
-        auto consider = [&](int lines, int w, int win) {
+        auto consider = [&](const Choice &c) {
             // the step's own jobs under this schedule (their fields depend on it)
             std::vector<iga_plan *> second;
             std::vector<iga_plan *> middle;
@@ -444,31 +448,40 @@ iga_status iga_ensemble_autotune(iga_ensemble *ens, void *const *T, void *const 
             });
             if (ms >= 0 && ms < best_ms) {
                 best_ms = ms;
-                best_l = lines;
-                best_w = w;
-                best_win = win;
+                best = c;
             }
         };
-        if (set_line_all(ens, dir)) consider(1, 0, 2);
+        // members that can solve one line per lane; their tables do not depend on
+        // the schedule beneath, which then only the other members run
+        std::vector<char> can(n, 0);
+        const bool any = set_line_all(ens, dir);
+        bool every = true;
+        for (size_t m = 0; m < n; ++m) {
+            can[m] = (char)ens->plans[m]->sched[dir].line;
+            every = every && can[m];
+        }
+        if (every) consider(Choice{dir ? 2 : 4, 17, 1, true});
+        auto candidate = [&](int lines, int w, int win) {
+            consider(Choice{lines, w, win, false});
+            if (!any || every) return;
+            for (size_t m = 0; m < n; ++m) ens->plans[m]->sched[dir].line = can[m];
+            consider(Choice{lines, w, win, true});
+        };
         for (int mm : {9, 13, 17, 25, 33})
             for (int lines : {1, 2, 4, 8, 16})
-                if (set_window_all(ens, dir, lines, mm) == IGA_OK) consider(lines, mm, 1);
+                if (set_window_all(ens, dir, lines, mm) == IGA_OK) candidate(lines, mm, 1);
         for (int wpl : {1, 2, 4}) {
             for (int lines : {1, 2, 4, 8, 16}) {
                 if (lines * wpl > 16) continue;
                 if (set_schedule_all(ens, dir, lines, wpl) != IGA_OK) continue;
-                consider(lines, wpl, 0);
+                candidate(lines, wpl, 0);
             }
         }
-        if (!best_l) return fail(IGA_EUNSUPPORTED, "no line-solve schedule fits every member");
-        if (best_win == 2) {
-            if ((st = set_window_all(ens, dir, dir ? 2 : 4, 17))) return st;
-            (void)set_line_all(ens, dir);
-            continue;
-        }
-        if ((st = best_win ? set_window_all(ens, dir, best_l, best_w)
-                           : set_schedule_all(ens, dir, best_l, best_w)))
+        if (!best.lines) return fail(IGA_EUNSUPPORTED, "no line-solve schedule fits every member");
+        if ((st = best.win ? set_window_all(ens, dir, best.lines, best.w)
+                           : set_schedule_all(ens, dir, best.lines, best.w)))
             return st;
+        if (best.line) (void)set_line_all(ens, dir);
     }
     IGA_HIP(hipStreamSynchronize(s));
     ens->unbind();
