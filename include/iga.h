@@ -65,10 +65,10 @@ typedef enum { IGA_PR = 0, IGA_STRANG_CN = 1, IGA_EXPLICIT = 2 } iga_scheme;
 /* IGA_FP64: every kernel in double.
  * IGA_FP32_REFINE: state and right-hand sides in float with float
  * accumulation; the 1D LU factorisations are computed in double.  The steps'
- * line-per-lane solves (below) run in double and round their result once; the
- * windowed, column and exact solves run in float, each followed by one step of
- * iterative refinement whose residual b - A x0 is formed in double with the
- * double operator. */
+ * line-per-lane solves (below) run in double and round their result once (the
+ * change of the state, added to it in float); the windowed, column and exact
+ * solves run in float, each followed by one step of iterative refinement whose
+ * residual b - A x0 is formed in double with the double operator. */
 typedef enum { IGA_FP64 = 0, IGA_FP32_REFINE = 1 } iga_precision;
 
 typedef enum { IGA_WIND_CONST = 0, IGA_WIND_SINCOS = 1 } iga_wind_kind;

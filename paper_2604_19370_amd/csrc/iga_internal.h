@@ -137,7 +137,6 @@ struct DirHost {
     int n = 0, N = 0;
     double L = 0, h = 0;
     std::vector<double> knots;
-    std::vector<double> bv, bd;   // [e][a][q] basis values / first derivatives
     std::vector<double> xq;       // [e][q] physical quadrature points
     std::vector<double> wq;       // [q] Gauss weight * h / 2
     std::vector<double> M, K, G;  // bands [N][2P+1]

@@ -84,8 +84,6 @@ static void build_dir(DirHost &D, int n, int p, double L)
     std::vector<double> gx, gw;
     gauss_legendre(p + 1, gx, gw);
     const int nq = p + 1, W = 2 * p + 1;
-    D.bv.assign((size_t)n * nq * nq, 0.0);
-    D.bd.assign((size_t)n * nq * nq, 0.0);
     D.xq.assign((size_t)n * nq, 0.0);
     D.wq.assign(nq, 0.0);
     for (int q = 0; q < nq; ++q) D.wq[q] = gw[q] * 0.5 * D.h;
@@ -106,10 +104,6 @@ static void build_dir(DirHost &D, int n, int p, double L)
             D.xq[(size_t)e * nq + q] = D.knots[p + e] + xl;
             double v[4], dv[4];
             basis_ders(tl, p + e, p, xl, v, dv);
-            for (int r = 0; r <= p; ++r) {
-                D.bv[((size_t)e * nq + r) * nq + q] = v[r];
-                D.bd[((size_t)e * nq + r) * nq + q] = dv[r];
-            }
             // element contributions to M, K, G (row = test function)
             for (int r = 0; r <= p; ++r)
                 for (int c = 0; c <= p; ++c) {

@@ -19,10 +19,10 @@
 //
 // All arithmetic is in double, for float state too: the fields are read and
 // written in float, and the result is the double solve of the float data,
-// rounded once.  (An FP32 solve refined once with a double residual, which
-// this replaces in the steps, costs four substitutions for two and does not
-// get nearer: the vector units do double multiply-adds at the rate of unpacked
-// float ones.)
+// rounded once; a base field is then added in float, as the other solves do.
+// (An FP32 solve refined once with a double residual, which this replaces in the
+// steps, costs four substitutions for two and does not get nearer: the vector
+// units do double multiply-adds at the rate of unpacked float ones.)
 //
 // Strang's middle substep, T** = A^{-1} B T* = T* + A^{-1} D T* with D = B - A, is
 // the same solve with D T* formed from the tile as it is read (BAND), in a
@@ -104,9 +104,9 @@ template <int P> struct LineOp {
     const double *rows, *meet;   // edge rows [nrows][LROW], py and pc of each edge chunk
 };
 template <int P> struct LineJob {
-    const void *src, *base;
+    const void *src, *base;   // base: y-lines, not BAND; or NULL
     void *dst;
-    int zero_skip;   // all-zero window: write zeros (no base) or nothing (dst == base)
+    int zero_skip;   // y-lines with dst == base: an all-zero window is left alone
     LineOp<P> a;
     double d[2 * P + 1];   // BAND: canonical row of D,
     const double *dend;    // and [4P+1][LBAND]: its rows [0, 2P), that one, [N-2P, N)
@@ -379,7 +379,7 @@ __device__ __forceinline__ void line_tile(const LineParams<P> &prm, const LineJo
     };
     auto pin = [&] {
         a.pin();
-        if (!BAND) asm volatile("" : "+v"(nz));
+        if (DIRY && !BAND) asm volatile("" : "+v"(nz));
     };
     // forward over the lower halo and the chunk
     if constexpr (BAND) {
@@ -396,7 +396,7 @@ __device__ __forceinline__ void line_tile(const LineParams<P> &prm, const LineJo
             b = dband(r0 - HL + i);
         } else {
             const T v = at(i);
-            nz |= line_bits(v);
+            if (DIRY) nz |= line_bits(v);
             b = (double)v;
         }
         const double y = a.fwd(b, i);
@@ -419,7 +419,7 @@ __device__ __forceinline__ void line_tile(const LineParams<P> &prm, const LineJo
             b = dband(r0 + MM + i);
         } else {
             const T v = at(HL + MM + i);
-            nz |= line_bits(v);
+            if (DIRY) nz |= line_bits(v);
             b = (double)v;
         }
         a.back(b, i);
@@ -433,23 +433,17 @@ __device__ __forceinline__ void line_tile(const LineParams<P> &prm, const LineJo
 #pragma unroll
         for (int i = 0; i < MM; ++i) a.y[i] += (double)at(P + HL + i);
     }
-    // the solve of zero data is exactly zero, and dst == base holds its sum
-    const bool skip = !BAND && job.zero_skip && job.base && !__any(nz != 0);
     if constexpr (!DIRY) {
-        const bool live = line0 + lane < prm.nlines;
-        if (skip) return;
         if (!BAND) a.finish(meet);
         T *d = static_cast<T *>(job.dst) + line0 + lane;
-        const T *bx = static_cast<const T *>(job.base) + line0 + lane;
-        if (live) {
+        if (line0 + lane < prm.nlines) {
 #pragma unroll
             for (int i = 0; i < MM; ++i)
-                if (!EDGE || r0 + i < N) {
-                    const size_t o = (size_t)(r0 + i) * ld;
-                    d[o] = (T)(!BAND && job.base ? a.y[i] + (double)bx[o] : a.y[i]);
-                }
+                if (!EDGE || r0 + i < N) d[(size_t)(r0 + i) * ld] = (T)a.y[i];
         }
     } else {
+        // the solve of zero data is exactly zero, and dst == base holds its sum
+        const bool skip = !BAND && job.zero_skip && !__any(nz != 0);
         if (!EDGE) request(job.base && !skip);
         if (!BAND) a.finish(meet);
         __syncthreads();   // every wavefront has read its rows of the tile

@@ -253,14 +253,14 @@ iga_status choose_line_schedule(iga_plan *pl, int dir)
     return IGA_OK;
 }
 
-// out of place: single solves (with a base field or not), or, alone in its
-// launch, Strang's middle substep along y
+// out of place: single solves (along y with a base field or not), or, alone in
+// its launch, Strang's middle substep along y
 bool line_jobs_ok(const iga_plan *pl, int dir, const SweepJob *jobs, int njobs)
 {
     if (!pl->sched[dir].line || njobs < 1 || njobs > LMAXJOBS) return false;
     for (int i = 0; i < njobs; ++i) {
         const SweepJob &j = jobs[i];
-        if (j.src == j.dst) return false;
+        if (j.src == j.dst || (dir == 0 && j.base)) return false;
         const bool single = j.op0 >= 0 && op_dir(j.op0) == dir && j.band < 0 && j.op1 < 0;
         const bool middle = dir == 1 && njobs == 1 && j.op0 < 0 && j.band == BAND_BY && j.op1 == OP_AY &&
                             !j.base && j.add_after;
@@ -290,7 +290,7 @@ static LineLaunch fill(const iga_plan *pl, int dir, const SweepJob *jobs, int nj
         q.src = j.src;
         q.base = j.base;
         q.dst = j.dst;
-        q.zero_skip = j.zero_skip && (!j.base || j.base == j.dst);
+        q.zero_skip = j.zero_skip && j.base && j.base == j.dst;
         std::memcpy(&q.a.k, pl->line_const[op].data(), sizeof q.a.k);
         const double *tab = pl->line_tab[dir].as<double>();
         const int first = (op == OP_MX || op == OP_MY) ? 2 : 0;
