@@ -8,8 +8,9 @@ wind (1 + 0.3 sin 2 pi y^, 0.5 cos 2 pi x^)).  The headline value is the
 FP32-with-FP64-refinement stepper in DOF-steps/s; the FP64 stepper on the same
 inputs is reported beside it.
 
-One JSON line on stdout.  `roofline` describes the dominant kernel of the FP32
-step (measured here with HIP events on the stream it runs on);
+One JSON line on stdout.  `roofline` describes the longest of the FP32 step's
+kernels that an entry point launches alone (measured here with HIP events on the
+stream it runs on);
 `cpu_baseline` is the FP64 CPU oracle timed on the host cores on a bounded
 sample of the same workload.
 """
@@ -39,8 +40,8 @@ def parse():
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--kernel-reps", type=int, default=50)
     ap.add_argument("--kernels-only", action="store_true",
-                    help="only launch each kernel of the FP32 step --kernel-reps times, plus a "
-                         "copy kernel of known size (for profiler runs)")
+                    help="only take --kernel-reps FP32 steps, launch each phase of a step that has an "
+                         "entry point as often, and a copy kernel of known size (for profiler runs)")
     ap.add_argument("--tune", action="store_true",
                     help="with --kernels-only: autotune first (as the timed runs do)")
     ap.add_argument("--schedule", type=str, default=None,
@@ -136,8 +137,12 @@ def precision_errors(pl32, T32, F32, pl64, T64, F64, sc, torch):
 
 
 def kernel_times(pl, sc, reps, torch):
-    """Average duration of each kernel of one step, launched through the C ABI
-    on one stream between HIP events (same grids as inside the step)."""
+    """Average duration of the entry points that run one phase, launched through
+    the C ABI on one stream between HIP events: iga_assemble_rhs (for FP32 plans
+    the step's own assemblies; FP64 plans return the direct form, their steps
+    assemble the increment) and iga_line_solve (in place, on the schedule beneath
+    the steps' line-per-lane sweeps: the step's own sweeps only where
+    Plan.line_per_lane is false)."""
     dt = pl.dtype
     T = torch.tensor(sc.T0, dtype=dt, device="cuda")
     F = torch.tensor(sc.fuel0, dtype=dt, device="cuda")
@@ -148,9 +153,9 @@ def kernel_times(pl, sc, reps, torch):
     cases = {
         "assemble_s1_fuel": lambda: pl.assemble_rhs(0, T, F, R, RF, stream),
         "assemble_s3": lambda: pl.assemble_rhs(2, T, F, R, None, stream),
-        "sweep_x_A": lambda: pl.line_solve(0, 0, X, stream),
-        "sweep_y_M": lambda: pl.line_solve(1, 1, X, stream),
-        "sweep_y_cn": lambda: pl.line_solve(1, 2, X, stream),
+        "line_solve_x_A": lambda: pl.line_solve(0, 0, X, stream),
+        "line_solve_y_M": lambda: pl.line_solve(1, 1, X, stream),
+        "line_solve_y_cn": lambda: pl.line_solve(1, 2, X, stream),
     }
     with torch.cuda.stream(stream):
         for name, fn in cases.items():
@@ -163,7 +168,7 @@ def kernel_times(pl, sc, reps, torch):
             e1.record(stream)
             torch.cuda.synchronize()
             out[name] = e0.elapsed_time(e1) / 1e3 / reps
-            if name.startswith("sweep"):
+            if name.startswith("line_solve"):
                 X.copy_(torch.randn_like(X))
     return out
 
@@ -184,14 +189,19 @@ def assembly_flops(p, fuel):
     return 2 * fma + pointwise * q * q
 
 
-# counter-summary entries per kernel of the step (the first one present is
-# used: x-lines run windowed or, where the autotuner picks them, by column waves)
+# counter-summary entries per kernel (the first one present is used): the step's
+# assemblies and line-per-lane sweeps, and the kernels of iga_line_solve (x-lines
+# run windowed or, where the autotuner picks them, by column waves)
 KERNEL_FAMILY = {"assemble_s1_fuel": ("k_assemble<float,p=2,fuel=true>",),
                  "assemble_s3": ("k_assemble<float,p=2,fuel=false>",),
-                 "sweep_x_A": ("k_wsweep<float,p=2,x-lines>", "k_csweep<2,32>", "k_csweep<2,16>"),
-                 "sweep_y_M": ("k_wsweep<float,p=2,y-lines>",),
-                 "sweep_y_cn": ("k_wsweep<float,p=2,y-lines>",)}
+                 "sweep_x_A": ("k_line<float,p=2,x-lines>",),
+                 "sweep_y_M": ("k_line<float,p=2,y-lines>",),
+                 "sweep_y_cn": ("k_line<float,p=2,y-lines,band>",),
+                 "line_solve_x_A": ("k_wsweep<float,p=2,x-lines>", "k_csweep<2,32>", "k_csweep<2,16>"),
+                 "line_solve_y_M": ("k_wsweep<float,p=2,y-lines>",),
+                 "line_solve_y_cn": ("k_wsweep<float,p=2,y-lines>",)}
 SOURCES = {"k_assemble": ("assemble.h", "assemble.hip"),
+           "k_line": ("sweep_line.h", "sweep_line.hip"),
            "k_wsweep": ("sweep_win.h", "sweep_kernels.h", "sweep.hip"),
            "k_csweep": ("sweep_col.h", "sweep_col.hip")}
 
@@ -235,13 +245,18 @@ def ambient_elements(sc):
     return int(e.sum())
 
 
-def roofline(kt, p, ndof, nel, nel_x, ambient=0):
-    """Roofline entry of the dominant (longest) kernel of the FP32 step.
+def roofline(kt, p, ndof, nel, nel_x, sched, ambient=0):
+    """Roofline entry of the longest of the kernels timed alone that the FP32 step
+    runs: the assemblies, and the line solves of a direction (sched[dir]) that the
+    steps do not solve one line per lane.
     ambient: elements the assembly skips (their flops are not counted)."""
     w = 4
     alg_bytes = {"assemble_s1_fuel": 4 * w * ndof, "assemble_s3": 3 * w * ndof,
-                 "sweep_x_A": 2 * w * ndof, "sweep_y_M": 2 * w * ndof, "sweep_y_cn": 2 * w * ndof}
-    dom = max(kt, key=kt.get)
+                 "line_solve_x_A": 2 * w * ndof, "line_solve_y_M": 2 * w * ndof,
+                 "line_solve_y_cn": 2 * w * ndof}
+    direction = {"line_solve_x_A": 0, "line_solve_y_M": 1, "line_solve_y_cn": 1}
+    own = [k for k in kt if k not in direction or not sched[direction[k]]["line_per_lane"]]
+    dom = max(own, key=kt.get)
     traffic = measured_traffic(dom, nel_x)
     roof = {"kernel": dom}
     if dom.startswith("assemble"):
@@ -272,6 +287,13 @@ def copy_kernel(n_bytes, reps, torch):
     for _ in range(reps):
         torch.neg(src, out=dst)
     torch.cuda.synchronize()
+
+
+def schedules(pl):
+    """Both directions (the schedule of iga_line_solve, and whether the steps solve
+    one line per lane instead) and the assembly's tiles."""
+    return [dict(pl.schedule(d), **pl.solver(d), line_per_lane=pl.line_per_lane(d)) for d in (0, 1)] + \
+        [{"assembly_rows": pl.assembly_rows, "assembly_stacked": pl.assembly_stacked}]
 
 
 def apply_schedule(pl, spec, windowed=False):
@@ -487,9 +509,7 @@ def stepper_leg(sc, steps, warmup, args, torch, iga):
         del Tt, Ft
         wall, ev, T, F = time_steps(pl, sc, steps, warmup, torch)
         res[prec] = dict(wall=wall, ev=ev, dofs=sc.ndof * steps / wall,
-                         sched=[dict(pl.schedule(0), **pl.solver(0)),
-                                dict(pl.schedule(1), **pl.solver(1)),
-                                {"assembly_rows": pl.assembly_rows, "assembly_stacked": pl.assembly_stacked}])
+                         sched=schedules(pl))
         ktimes[prec] = kernel_times(pl, sc, args.kernel_reps, torch)
         plans[prec], finals[prec] = pl, (T, F)
     errs = precision_errors(plans["fp32"], *finals["fp32"], plans["fp64"], *finals["fp64"], sc, torch)
@@ -499,8 +519,8 @@ def stepper_leg(sc, steps, warmup, args, torch, iga):
 
 def config_4096(args, torch, iga, inputs):
     """The precision form at scale: 4096^2 quadratic, Strang-CN, FP32+refine
-    against FP64 on the same inputs, with the roofline of its dominant
-    kernel and the whole step against HBM."""
+    against FP64 on the same inputs, with the roofline of its longest
+    assembly and the whole step against HBM."""
     sc = inputs.regional_strang(seed=1, nel=4096, steps=args.steps)
     plans, res, ktimes, errs = stepper_leg(sc, args.steps, args.warmup, args, torch, iga)
     for pl in plans.values():
@@ -516,7 +536,7 @@ def config_4096(args, torch, iga, inputs):
            "fp32_over_fp64": round(res["fp32"]["dofs"] / res["fp64"]["dofs"], 3),
            "step_hbm_frac": round(res["fp32"]["dofs"] * 60 / (HBM_PEAK_GBS * 1e9), 4),
            "roofline": roofline(kt, sc.p, sc.ndof, sc.nel_x * sc.nel_y, sc.nel_x,
-                                ambient_elements(sc)),
+                                res["fp32"]["sched"], ambient_elements(sc)),
            "fp32_vs_fp64": errs,
            "schedules": res["fp32"]["sched"]}
     return out
@@ -547,12 +567,14 @@ def main():
             Ft = torch.tensor(sc.fuel0, dtype=pl.dtype, device="cuda")
             pl.autotune(Tt, Ft, reps=10)
             del Tt, Ft
+        T = torch.tensor(sc.T0, dtype=pl.dtype, device="cuda")
+        F = torch.tensor(sc.fuel0, dtype=pl.dtype, device="cuda")
+        for _ in range(args.kernel_reps):
+            pl.step(T, F)
         kt = kernel_times(pl, sc, args.kernel_reps, torch)
         copy_kernel(4 * sc.ndof, args.kernel_reps, torch)
         print(json.dumps({"kernel_us": {k: round(v * 1e6, 2) for k, v in kt.items()},
-                          "schedules": [dict(pl.schedule(0), **pl.solver(0)),
-                                        dict(pl.schedule(1), **pl.solver(1)),
-                                        {"assembly_rows": pl.assembly_rows, "assembly_stacked": pl.assembly_stacked}],
+                          "schedules": schedules(pl),
                           "copy_bytes": 4 * sc.ndof}), flush=True)
         pl.close()
         return
@@ -561,7 +583,7 @@ def main():
     kt = ktimes["fp32"]
     ndof = sc.ndof
     nel = sc.nel_x * sc.nel_y
-    roof = roofline(kt, sc.p, ndof, nel, sc.nel_x, ambient_elements(sc))
+    roof = roofline(kt, sc.p, ndof, nel, sc.nel_x, res["fp32"]["sched"], ambient_elements(sc))
 
     line = {
         "metric": "DOF-steps/s at 1024^2 quadratic IGA (Strang-CN), FP32+refine; FP64 beside",
@@ -574,7 +596,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (1D LU and refinement residual f64)",
+        "dtype": "f32 (1D LU and the steps' line solves f64)",
         "data": "synthetic",
         "config": {"workload": f"regional Strang-CN {sc.nel_x}x{sc.nel_y} quadratic, dt 5e-4",
                    "dofs": ndof, "elements": nel, "steps": args.steps},
