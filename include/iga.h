@@ -117,7 +117,8 @@ void iga_default_coeffs(iga_coeffs *out);
 /* Build a plan: knots, Gauss rules, wind samples at the quadrature points, the
  * 1D matrices M, K, G (Section 3.1) and the directional operators of the
  * scheme, uploaded to the current HIP device.  Allocates device memory (tables
- * and scratch of 4 fields).  *out is NULL on failure.
+ * and scratch of 4 fields; of 2 in FP64, where iga_factor_1d takes the other 2
+ * for the line-per-lane solves).  *out is NULL on failure.
  * Errors: IGA_EINVAL (NULL pointers, p not in {1,2,3}, nel < 2p+1, lengths or dt
  * not > 0, unknown enum), IGA_ENOMEM, IGA_EDEVICE. */
 iga_status iga_plan_create(const iga_plan_desc *desc, iga_plan **out);
@@ -138,9 +139,11 @@ iga_status iga_plan_dims(const iga_plan *plan, int64_t *nx, int64_t *ny, int64_t
  * chunks of 16 rows per workgroup, each chunk eliminated in double from both
  * sides, from a zero state so many rows outside it that the restart changes
  * nothing above rounding (as for windowed solves, below).  Where an operator
- * decays too slowly for the rows compiled in, and from the next call on that
- * sets a schedule of the direction, the steps use that direction's windowed,
- * column or exact schedule; iga_line_solve, which works in place, always does. */
+ * decays too slowly for the rows compiled in, where lines are shorter than
+ * 4p + 1 dofs or their scratch fields cannot be allocated, and from the next call
+ * on that sets a schedule of the direction, the steps use that direction's
+ * windowed, column or exact schedule (iga_plan_line_per_lane says which);
+ * iga_line_solve, which works in place, always does. */
 iga_status iga_factor_1d(iga_plan *plan, void *stream);
 
 /* Quadrature right-hand side of one substep (weak forms eq. varPR_wildfire
@@ -230,12 +233,13 @@ iga_status iga_run(iga_plan *plan, void *T, void *fuel, int64_t nsteps, void *st
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the step of
  * iga_step, with the right-hand-side scratch taken from a fixed device array
- * of IGA_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on
- * until the process ends, instead of the plan's own buffers.  Calls no
- * allocating routine.  The plan is accepted up to 2 fields (4 under column-wave x
- * sweeps) of ndof * element size bytes, each rounded up to 256 bytes; a plan
- * that needs more returns IGA_EINVAL (so at most about 8.3M dofs for FP32
- * plans, 4.1M for FP64).  The first call on a device looks the array's
+ * that the library holds on each GPU it runs on until the process ends, instead
+ * of the plan's own buffers.  Calls no allocating routine.  A plan is accepted
+ * where 2 fields (4 under column-wave x sweeps) of ndof * element size bytes,
+ * each rounded up to 256 bytes, fit IGA_NOALLOC_SCRATCH_BYTES, and IGA_EINVAL
+ * is returned otherwise (so at most about 8.3M dofs for FP32 plans, 4.1M for
+ * FP64).  The array is twice that size, 128 MiB: line-per-lane sweeps write a
+ * second pair of fields.  The first call on a device looks the array's
  * address up once.  Every call on one GPU shares its array, which keeps the
  * last call's contents (nothing in it has to start at zero): calls that
  * overlap on one GPU -- two streams, or two host threads -- race, and the
