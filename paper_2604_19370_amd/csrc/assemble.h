@@ -259,8 +259,10 @@ __device__ __forceinline__ void from_uniform(T (&r)[P + 1], int e, int n)
 // together with the points' exponentials side by side 1500^2 cubic in double
 // 422 -> 400).  Constants of the points in vector registers (double, p <= 2):
 // 4096^2 1126 -> 1116 us a step.  Against tables per element and column in registers
-// (p = 2: 36 of them), which this replaced: FP32 113-122 registers for 152-168
-// (4 wavefronts per SIMD for 3), double 215-227 for 340 (2 for 1).  Both
+// (p = 2: 36 of them), which this replaced: FP32 108-120 registers for 152-168
+// (4 wavefronts per SIMD for 3), double 237-253 (the test functions' values
+// among them) for 340 (2 for 1).  p = 3 takes 168-189 in FP32 (2 wavefronts) and
+// 325-362 in double (1, and 45-93 scalar registers spilled to vector lanes).  Both
 // assemblies of a Strang step, best tiles: FP32 4096^2 155 + 140 -> 109 + 101 us,
 // 1024^2 24.0 + 22.8 -> 19.2 + 17.1, cubic 4096^2 399 + 347 -> 284 + 260; direct
 // form in double 4096^2 578 + 408 -> 415 + 250, cubic 1562 + 946 -> 1527 + 830.
@@ -780,16 +782,8 @@ __device__ __forceinline__ void assemble_group(const AsmParams<T> &a, CT<AsmPara
     }
 }
 
-// Occupancy target: float cubic kernels sit a few registers above the 256
-// that allow two wavefronts per SIMD; asking for two costs a couple of
-// spilled registers and doubles the wavefronts in flight.  Elsewhere the
-// compiler's own allocation stands.
-template <typename T, int P> struct AsmWaves {
-    static constexpr int value = (sizeof(T) == 4 && P == 3) ? 2 : 1;
-};
-
 template <typename T, int P, bool FUEL, bool SRC, bool STK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AsmWaves<T, P>::value)))
+__global__ __launch_bounds__(256)
 void k_assemble(AsmParams<T> a)
 {
     // the record is the only argument: the kernel's argument segment
@@ -800,7 +794,7 @@ void k_assemble(AsmParams<T> a)
 // Batched launch over the members of an ensemble: workgroup b does workgroup
 // info[b].y of member info[b].x (x < 0: no work).
 template <typename T, int P, bool FUEL, bool STK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AsmWaves<T, P>::value)))
+__global__ __launch_bounds__(256)
 void k_assemble_batch(const AsmParams<T> *__restrict__ prms, const int2 *__restrict__ info)
 {
     const int2 wi = info[blockIdx.x];

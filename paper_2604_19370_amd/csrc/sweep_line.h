@@ -60,8 +60,11 @@ template <> struct LineHalo<double, 1> { static constexpr int value = 32; };
 template <> struct LineHalo<double, 2> { static constexpr int value = 48; };
 template <> struct LineHalo<double, 3> { static constexpr int value = 72; };
 
-// Wavefronts (chunks of MM rows) per workgroup: as many as leave room for a
-// second workgroup beside it in LDS, whose loads overlap this one's solves.
+// Wavefronts (chunks of MM rows) per workgroup.  Other workgroups beside it in
+// LDS load while it solves: five, four and three share a compute unit in float
+// (29, 35, 43 KB), two in double for p <= 2 (67, 77 KB).  For p = 3 in double no
+// number of wavefronts leaves room for a second one (the halo rows alone take
+// 72 KB); six share the halos of one workgroup (131 KB).
 constexpr int LINE_MM = 16;
 template <typename T, int P> struct LineWaves;
 template <> struct LineWaves<float, 1> { static constexpr int value = 4; };
