@@ -92,6 +92,16 @@ template <typename T> __device__ __forceinline__ CT<T> *as_const(const T *p)
     return (CT<T> *)p;
 }
 
+// a pointer read from memory, known to point to device memory: through it the
+// compiler issues global accesses, which do not count as LDS ones (flat ones do,
+// and every wait for LDS data waits for them too)
+template <typename T> __device__ __forceinline__ T *as_global(T *p)
+{
+    auto g = (__attribute__((address_space(1))) T *)p;
+    asm("" : "+s"(g));   // (or the two casts cancel)
+    return (T *)g;
+}
+
 // ---------------------------------------------------------------------------
 // One element in the uniform basis
 // ---------------------------------------------------------------------------
@@ -799,7 +809,18 @@ void k_assemble_batch(const AsmParams<T> *__restrict__ prms, const int2 *__restr
 {
     const int2 wi = info[blockIdx.x];
     if (wi.x < 0) return;   // the whole workgroup
-    assemble_group<T, P, FUEL, false, STK>(prms[wi.x], as_const(prms + wi.x), wi.y);
+    // read once, before any store: read where it is used, the record is fetched
+    // again after every store that might have changed it (with global accesses,
+    // both assemblies of 16 cubic 2048^2 members in FP32: 1509 + 1145 -> 1022 + 920 us;
+    // with the fuel accumulators in registers, before they moved to LDS, 1216 + 1181)
+    AsmParams<T> a = prms[wi.x];
+    a.S = as_global(a.S);
+    a.F = as_global(a.F);
+    a.R = as_global(a.R);
+    a.RF = as_global(a.RF);
+    a.wx = as_global(a.wx);
+    a.wy = as_global(a.wy);
+    assemble_group<T, P, FUEL, false, STK>(a, as_const(prms + wi.x), wi.y);
 }
 
 // The compiled kernel of degree P: unforced or forced (SRC), stacked or not,
