@@ -255,8 +255,10 @@ iga_status iga_factor_1d(iga_plan *plan, void *stream)
         if ((st = build_scan_tables(plan, dir)) || (st = choose_schedule(plan, dir, 0, 0))) return st;
     }
     // and, for the steps, line-per-lane solves on top where they are possible
-    for (int dir = 0; dir < 2; ++dir)
+    for (int dir = 0; dir < 2; ++dir) {
+        plan->line_state[dir] = 0;
         if (choose_line_schedule(plan, dir)) (void)hipGetLastError();
+    }
     set_error("");
     plan->factored = true;
     plan->graph.reset();

@@ -203,6 +203,7 @@ struct iga_plan {
     iga::DevBuf line_tab[2];
     std::vector<double> line_const[iga::NOPS], line_d;
     iga::LineGeom line_geom[2];
+    int line_state[2] = {0, 0};   // since the factorisation: 1 tables built, -1 refused
     iga::DevBuf flag;                          // non-finite detector
     bool factored = false;
     iga::GraphCache graph;

@@ -340,41 +340,48 @@ int compute_warmup(const OpHost &o, int N, int P, double tol, int hmax)
 {
     const int RS = 2 * P + 2;
     auto row = [&](int r) { return &o.rows[(size_t)row_of(r, o.K0, o.NK, o.nrows) * RS]; };
-    auto worst = [&](bool fwd) {
-        std::vector<int> starts;
-        for (int s = 0; s < std::min(N, o.K0 + hmax + 2); ++s) starts.push_back(s);
-        for (int s = std::max(0, o.NK - hmax - 2); s < N; ++s) starts.push_back(s);
-        int h_need = 0;
-        for (int s : starts) {
-            std::vector<double> m((size_t)P * P, 0.0), n((size_t)P * P);
-            for (int i = 0; i < P; ++i) m[(size_t)i * P + i] = 1.0;
-            int h = 0;
-            for (;;) {
-                const int r = fwd ? s + h : s - h;
-                if (r < 0 || r >= N) break;   // reached the line end: exact from here
-                const double *c = row(r);
-                // n = C_r m
-                for (int j = 0; j < P; ++j) {
-                    double v = 0.0;
-                    for (int k = 0; k < P; ++k) v -= (fwd ? c[k] : c[P + 1 + k]) * m[(size_t)k * P + j];
-                    n[j] = v;
-                }
-                for (int i = 1; i < P; ++i)
-                    for (int j = 0; j < P; ++j) n[(size_t)i * P + j] = m[(size_t)(i - 1) * P + j];
-                m.swap(n);
-                ++h;
-                double nrm = 0.0;
-                for (int i = 0; i < P; ++i) {
-                    double rs = 0.0;
-                    for (int j = 0; j < P; ++j) rs += std::fabs(m[(size_t)i * P + j]);
-                    nrm = std::max(nrm, rs);
-                }
-                if (nrm <= tol) break;
-                if (h > hmax) return hmax + 1;
+    // rows needed from start s
+    auto need = [&](bool fwd, int s) {
+        double m[3][3] = {};
+        for (int i = 0; i < P; ++i) m[i][i] = 1.0;
+        int h = 0;
+        for (;;) {
+            const int r = fwd ? s + h : s - h;
+            if (r < 0 || r >= N) break;   // reached the line end: exact from here
+            const double *c = row(r) + (fwd ? 0 : P + 1);
+            // m <- C_r m
+            double n[3];
+            for (int j = 0; j < P; ++j) {
+                n[j] = 0.0;
+                for (int k = 0; k < P; ++k) n[j] -= c[k] * m[k][j];
             }
-            h_need = std::max(h_need, h);
+            for (int i = P - 1; i > 0; --i)
+                for (int j = 0; j < P; ++j) m[i][j] = m[i - 1][j];
+            for (int j = 0; j < P; ++j) m[0][j] = n[j];
+            ++h;
+            double nrm = 0.0;
+            for (int i = 0; i < P; ++i) {
+                double rs = 0.0;
+                for (int j = 0; j < P; ++j) rs += std::fabs(m[i][j]);
+                nrm = std::max(nrm, rs);
+            }
+            if (nrm <= tol) break;
+            if (h > hmax) return hmax + 1;
         }
-        return h_need;
+        return h;
+    };
+    // starts whose rows are all canonical need what one of them does (span)
+    auto worst = [&](bool fwd) {
+        int h = 0, span = hmax + 1;
+        if (o.K0 < o.NK) {
+            h = need(fwd, fwd ? o.K0 : o.NK - 1);
+            if (h <= o.NK - o.K0) span = std::min(span, h);
+        }
+        const int head = std::min(N, o.K0 + (fwd ? 1 : span + 1));
+        const int tail = std::max(head, o.NK - (fwd ? span + 1 : 1));
+        for (int s = 0; s < head && h <= hmax; ++s) h = std::max(h, need(fwd, s));
+        for (int s = tail; s < N && h <= hmax; ++s) h = std::max(h, need(fwd, s));
+        return h;
     };
     const int h = std::max(worst(true), worst(false));
     return h > hmax ? 0 : h;

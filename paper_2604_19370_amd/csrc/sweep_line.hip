@@ -134,7 +134,7 @@ static bool canonical(const LineHostOp &h, std::vector<double> &k)
 // iga_line_solve keeps the direction's windowed or exact schedule.
 // IGA_EUNSUPPORTED if an operator decays too slowly for the compiled halo, has
 // long edges, or the lines are shorter than 4p + 1.
-iga_status choose_line_schedule(iga_plan *pl, int dir)
+static iga_status build_line(iga_plan *pl, int dir)
 {
     const int N = dir ? pl->Ny : pl->Nx, P = pl->P, RS = 2 * P + 2, LROW = line_row_size(P);
     const LineShape sh = line_shape(pl);
@@ -249,6 +249,22 @@ iga_status choose_line_schedule(iga_plan *pl, int dir)
     }
     pl->line_tab[dir] = std::move(tab);
     pl->line_geom[dir] = geom;
+    return IGA_OK;
+}
+
+// The tables depend on the operators alone: built once after a factorisation,
+// whatever schedules come and go beneath (ensembles and the autotuners lay the
+// solves over one schedule after another).
+iga_status choose_line_schedule(iga_plan *pl, int dir)
+{
+    int &state = pl->line_state[dir];
+    if (state < 0) return fail(IGA_EUNSUPPORTED, "no line-per-lane solves for these operators");
+    if (!state) {
+        const iga_status st = build_line(pl, dir);
+        if (st == IGA_EUNSUPPORTED) state = -1;
+        if (st) return st;
+        state = 1;
+    }
     pl->sched[dir].line = 1;
     return IGA_OK;
 }
