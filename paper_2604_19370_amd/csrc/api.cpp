@@ -76,8 +76,9 @@ iga_status check_field(const void *p, const char *name)
 // adds the state it was taken from.  FP32 needs it (the float right-hand side
 // then carries only the O(tau) change); FP64 gains the terms that are zero away
 // from the fire, the fuel sweeps and ambient elements among them, for one more
-// field read per y sweep.  A PR or Strang step is six launches:
-// assembly, x sweep, y sweep, twice; an explicit step is the first three.
+// field read per y sweep.  A PR step is six launches: assembly, x sweep, y sweep,
+// twice; a Strang step is these, or seven where S2 is a sweep of its own (under a
+// line-per-lane y schedule); an explicit step is the first three.
 // The x sweeps solve in place, or into second scratch fields under a
 // column-wave or line-per-lane x schedule (whose waves read rows around their
 // own chunk); so does Strang's fused y sweep under a line-per-lane y schedule.

@@ -1,6 +1,6 @@
-// plan.cpp -- host side of a plan: knot vectors, Gauss rules, B-spline basis
-// tables at the quadrature points, the 1D matrices M, K, G of Section 3.1 and
-// the directional operators of the two schemes, and their upload.
+// plan.cpp -- host side of a plan: knot vectors, Gauss rules, wind samples at
+// the quadrature points, the 1D matrices M, K, G of Section 3.1 and the
+// directional operators of the two schemes, and their upload.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
